@@ -56,10 +56,11 @@ enum {
 /* Solver pass that produced an instance's result (gwtf_mcf_get_passes). */
 enum {
     GWTF_PASS_REGISTER = 1, /* one workgroup, link costs in registers: 16 < n <= 64, S <= 32 */
-    GWTF_PASS_LDS = 2,      /* one workgroup, instance state in LDS: n <= 64 */
+    GWTF_PASS_LDS = 2,      /* instance state in LDS: n <= 64 (several per wave for n <= 16, S <= 16) */
     GWTF_PASS_GRID = 3,     /* each instance over S * ceil(n/128) co-resident workgroups: 64 < n <= 512, or 16 < n <= 64 with S > 32 in small batches */
-    GWTF_PASS_GLOBAL = 4,   /* one workgroup, instance state in device memory: any shape */
-    GWTF_PASS_PACKED = 5    /* 1 to 8 instances per wave (8 only for n <= 8): S <= 8, supply <= 255, costs <= 2047 */
+    GWTF_PASS_GLOBAL = 4,   /* instances outside the bounds of their shape's pass, any shape (state in device
+                               memory; on chip for S <= 8, n <= 16) */
+    GWTF_PASS_PACKED = 5    /* 1 to 16 instances per wave: S <= 8, n <= 16, supply <= 255, costs <= 2047 */
 };
 
 /* arc_cost entry meaning "these two nodes share no link". */
@@ -120,7 +121,9 @@ gwtf_status_t gwtf_mcf_get_flows(gwtf_mcf_t *h, int32_t first, int32_t count,
  * flow-list (reverse-arc) relaxations, the nanoseconds the instance's
  * workgroup spent in forward sweeps, backward sweeps, augmentation with the
  * potential update, and the rest (label reset, sink update), then the
- * executed forward and backward layer steps (0 where not tracked).  For
+ * executed forward and backward layer steps (0 where not tracked).  The
+ * register pass and the passes with several instances per wave report both
+ * sweeps in the first of the four clocks, those of the instance's wave.  For
  * instances of the grid pass (GWTF_PASS_GRID) the clocks are workgroup 0's:
  * label iterations, then 0, then the potential update with the path walks
  * and augmentations of a search (tied exits included), then the rest (label

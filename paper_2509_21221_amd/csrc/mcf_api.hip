@@ -277,12 +277,13 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
     const int waves = lds_waves(n);
     const int64_t slots = pipe_slots > 0 ? 0 : lds_slots(S, n, waves, d.lds_max);
     if (small_pass_fits(S, n)) {
-        // Four instances per wave; instances outside the packed bounds go to
-        // the fallback pass.
+        // Up to sixteen instances per wave; a second launch solves those
+        // outside the first one's bounds, so no fallback pass follows.
         p.list_slots = 0;
         p.route_all = 0;
-        if ((e = launch_small_pass(p, stream)) != hipSuccess) return {GWTF_ERR_DEVICE, "packed solver launch", e};
-        need_fallback = true;
+        if ((e = launch_small_pass(p, d.lds_max, stream)) != hipSuccess)
+            return {GWTF_ERR_DEVICE, "packed solver launch", e};
+        need_fallback = false;
     } else if (w.grid && grid_preferred(w, n, p.B)) {
         // Cooperative launches of up to grid_conc instances each; instances
         // whose link costs need more than 16 bits or whose flow lists outgrow

@@ -91,7 +91,7 @@ __host__ __device__ inline size_t scratch_bytes(int waves, int n)
     return align16(size_t(8) * waves * n) + align16(size_t(4) * waves * 64);
 }
 
-// Launchers (mcf_solver.hip).  Return the HIP launch status.
+// Launchers (mcf_solver.hip; the packed pass's are in mcf_small.h).  Return the HIP launch status.
 hipError_t launch_lds_pass(const SolveParams &p, int waves, size_t lds_bytes, hipStream_t s);
 hipError_t launch_fallback_pass(const SolveParams &p, size_t lds_bytes, hipStream_t s);
 hipError_t launch_export(const int32_t *node_flow_ws, int32_t S, int32_t n, int32_t first, int32_t count,

@@ -1,0 +1,113 @@
+"""The packed pass over its whole range against the oracle: every group width
+(4, 8 and 16 lanes), shallow and deep pipelines, and the three value ranges it
+tells apart (8-bit flows and small costs; 16-bit flows and costs while labels
+stay below 2^25; anything beyond, solved one instance per wave), also mixed in
+one batch.  All results are whole numbers: no tolerance."""
+import numpy as np
+import pytest
+
+import mcf_checks as C
+import oracle
+from gpu_util import gpu_solve
+from paper_2509_21221_amd import mcf
+from paper_2509_21221_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def compare(batch, g, certify=8):
+    ref = oracle.solve(batch, flows=False, potentials=False)
+    for key in ("status", "F", "cost"):
+        np.testing.assert_array_equal(g[key], ref[key], err_msg=key)
+    for b in [b for b in range(batch.B) if g["status"][b] == 0][:certify]:
+        C.certify(batch, b, int(g["F"][b]), int(g["cost"][b]), g["node_flow"][b], g["arc_flow"][b],
+                  g["src_flow"][b], g["snk_flow"][b], g["potential"][b])
+
+
+def expected(batch):
+    """Pass of each valid instance: a shallow one outside the packed bounds
+    is reported as the fallback's, a deep one always as the LDS pass's."""
+    if batch.S > 8:
+        return np.full(batch.B, mcf.GWTF_PASS_LDS)
+    big = [np.abs(a).reshape(batch.B, -1).max(1, initial=0) for a in
+           (batch.node_cost, batch.arc_cost, batch.src_cost, batch.snk_cost)]
+    return np.where((batch.supply > 255) | (np.max(big, 0) > 2047), mcf.GWTF_PASS_GLOBAL, mcf.GWTF_PASS_PACKED)
+
+
+@pytest.mark.parametrize("n", [1, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("S", [1, 2, 8, 9, 16])
+def test_shapes_and_value_ranges(S, n):
+    """One batch per shape that mixes the three ranges, with missing links and
+    deleted nodes; the ranges' own edges (255 and 256, 2047 and 2048, 65,535
+    and 65,536 of flow value, labels about 2^25) in its first instances."""
+    wide = ((1 << 25) - (1 << 16)) // (2 * S * n + 3)  # largest cost with labels below the 16-bit form's bound
+    part = [W.random_small(12, S, n, seed=51 + i, cap_hi=cap, cost_hi=cost, supply_hi=supply, holes=0.1,
+                           zero_cap=0.1)
+            for i, (cap, cost, supply) in enumerate([(9, 2047, 255), (60, 2047, 255), (300, 50, 3000),
+                                                     (7, min(wide, 60000), 90), (7, wide + 1, 40),
+                                                     (200000, 30, 400000)])]
+    batch = W.concat(part)
+    batch.supply[0], batch.supply[1], batch.supply[2] = 255, 256, 2_000_000_000
+    batch.node_cost[3, 0, 0], batch.node_cost[4, 0, 0] = 2047, 2048
+    batch.node_cost[36, 0, 0], batch.node_cost[37, 0, 0] = wide - 1, wide
+    if n > 1:  # a flow value at the 16-bit bound and one above, over two nodes per stage
+        for b, extra in ((60, 0), (61, 1)):
+            batch.node_cap[b] = 0
+            batch.node_cap[b, :, 0], batch.node_cap[b, :, 1] = 65000, 535 + extra
+            batch.supply[b] = 1 << 20
+            if S > 1:
+                batch.arc_cost[b] = 3
+    print(f"packed ranges S={S} n={n}", flush=True)
+    g = gpu_solve(batch)
+    compare(batch, g)
+    for b in (36, 37, 48, 60, 61):
+        if g["status"][b] == 0:
+            C.certify(batch, b, int(g["F"][b]), int(g["cost"][b]), g["node_flow"][b], g["arc_flow"][b],
+                      g["src_flow"][b], g["snk_flow"][b], g["potential"][b])
+    ok = g["status"] == 0
+    np.testing.assert_array_equal(g["passes"][ok], expected(batch)[ok])
+
+
+@pytest.mark.parametrize("S,n,B", [(3, 3, 1024), (3, 3, 1025), (3, 3, 16400), (5, 7, 8193), (4, 10, 4097),
+                                   (12, 4, 2049), (10, 12, 1030)])
+def test_instances_per_wave(S, n, B):
+    """Batch sizes at which the instances per wave change, the last wave
+    partly empty; some instances in the wider range."""
+    batch = W.random_small(B, S, n, seed=61, cap_hi=5, cost_hi=300, supply_hi=2 * n + 4, holes=0.1, zero_cap=0.1)
+    batch.supply[::97] = 300
+    print(f"packed per wave S={S} n={n} B={B}", flush=True)
+    compare(batch, gpu_solve(batch))
+
+
+def zigzag(S, n):
+    """Two unit chains a and d that the first two paths take; the third must
+    enter at b, run back along a, over to c, back along d and out through e:
+    about 7 S nodes on one path."""
+    a, b, c, d, e = range(5)
+    x = W.random_small(1, S, n, seed=1, src_snk=False)
+    x.node_cap[:] = 1
+    x.node_cost[:] = 1
+    x.arc_cost[:] = W.NO_ARC
+    x.node_cap[0, 0, [c, e]] = 0
+    x.node_cap[0, :, 5:] = 0
+    x.node_cap[0, S - 1, [b, c]] = 0
+    for k in range(S - 1):
+        x.arc_cost[0, k, [a, d], [a, d]] = 1
+        x.arc_cost[0, k, [b, c, e], [b, c, e]] = 50
+    x.arc_cost[0, S - 2, b, a] = x.arc_cost[0, S - 2, c, d] = 50
+    x.arc_cost[0, 0, a, c] = x.arc_cost[0, 0, d, e] = 50
+    x.supply[:] = 9
+    return x
+
+
+@pytest.mark.parametrize("S,n,wide", [(8, 5, False), (16, 5, False), (16, 16, False), (16, 8, True)])
+def test_paths_longer_than_the_listed_nodes(S, n, wide):
+    """A path of more nodes than are listed at a time (64) is walked in
+    parts; the batch also holds instances with short paths."""
+    x = W.concat([zigzag(S, n), W.random_small(9, S, n, seed=62, cap_hi=4, cost_hi=90, supply_hi=30), zigzag(S, n)])
+    if wide:
+        x.supply[:] += 300
+    print(f"packed zigzag S={S} n={n}", flush=True)
+    g = gpu_solve(x)
+    assert g["F"][0] == 3 and g["F"][10] == 3
+    compare(x, g, certify=11)
