@@ -307,8 +307,10 @@ typedef struct {
     int32_t *node_flow, *arc_flow, *src_flow, *snk_flow;
 } gwtf_mcf_flow_out_t;
 
-/* One workgroup per instance holds the instance in LDS: requires S*n <= 512
- * and (S-1)*n*n <= 4096 (GWTF_ERR_INVALID_ARG otherwise, nothing enqueued).
+/* Instances are held on chip, several per wave for S <= 8 and n <= 16 with
+ * values up to 255 and costs up to 2047, one per workgroup otherwise: requires
+ * S*n <= 512 and (S-1)*n*n <= 4096 (GWTF_ERR_INVALID_ARG otherwise, nothing
+ * enqueued).
  * `out` may be NULL (no flows written; an instance that is not OK gets zero
  * flows).  `work` (device int64 [batch][4], or NULL) receives per instance
  * the paths removed, cycles cancelled, augmentations and label-correcting

@@ -18,6 +18,8 @@
 //      flow along a shortest path keeps it least-cost, so the result is the
 //      same optimum a cold solve reaches (Eq. 2).
 //
+// This is the general form, for pipelines of more than 8 stages or 16 nodes
+// and for the instances that the packed form (mcf_churn_packed.hip) passes on.
 // One workgroup per instance holds the whole instance in LDS.  Labels are
 // corrected in place (stage order is not needed: the residual graph is no
 // longer a DAG once cycles are cancelled) with one thread per vertex pulling
@@ -27,7 +29,7 @@
 // and at once when a label crosses that bound.  The check is pointer doubling:
 // after ceil(log2 V) + 1 rounds every vertex's ancestor is either a root
 // (never relabelled) or a vertex on a cycle.
-#include "mcf_internal.h"
+#include "mcf_churn.h"
 
 #include "gwtf_mcf.h"
 
@@ -255,6 +257,7 @@ __global__ void __launch_bounds__(kChurnThreads) churn_kernel(ChurnParams p)
     const int ld = n + 1, plinks = (S - 1) * n * ld; // padded rows in LDS
     const int tid = threadIdx.x, nt = blockDim.x;
     const int64_t b = blockIdx.x, s0 = p.start_per_instance ? b : 0;
+    if (p.passed_on && p.status_out[b] != kChurnPassedOn) return;
 
     Inst I;
     I.S = S;
@@ -515,7 +518,13 @@ hipError_t launch_churn_resolve(const ChurnParams &p, hipStream_t stream)
     // and more instances share a CU.
     const int V = 2 * p.S * p.n + 2;
     const int threads = V <= 192 ? 64 : kChurnThreads;
-    hipLaunchKernelGGL(churn_kernel, dim3(p.B), dim3(threads), churn_lds_bytes(p.S, p.n), stream, p);
+    ChurnParams q = p;
+    q.passed_on = p.S <= kChurnPackedStages && p.n <= 16;
+    if (q.passed_on) {
+        const hipError_t e = launch_churn_packed(p, stream);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(churn_kernel, dim3(p.B), dim3(threads), churn_lds_bytes(p.S, p.n), stream, q);
     return hipGetLastError();
 }
 
