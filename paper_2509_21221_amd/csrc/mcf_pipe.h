@@ -1,5 +1,5 @@
 // Internal interface of the stage-pipelined register pass
-// (mcf_solver_pipe.hip): one workgroup of 8 waves per instance, S <= 32,
+// (mcf_solver_pipe.hip): one workgroup of 8 or 16 waves per instance, S <= 32,
 // n <= 64, link costs below 65535.  Not part of the public C ABI.
 #pragma once
 
@@ -12,7 +12,7 @@ constexpr int kPipeMaxStages = 32;
 // Dynamic LDS of one workgroup: mailboxes per wave, node arrays [S][64]
 // (one row per stage), the path buffer and the flow lists.
 struct PipeLayout {
-    size_t exmb, enmb, nf, capl, ncl, chain, loff, llen, path, lamt, lent;
+    size_t exmb, enmb, nf, capl, ncl, words, loff, llen, path, lamt, lent;
     size_t total;
 };
 
@@ -27,10 +27,10 @@ __host__ __device__ inline PipeLayout pipe_layout(int S, int waves, int64_t slot
     L.nf = take(4 * rows);
     L.capl = take(4 * rows);
     L.ncl = take(4 * rows);
-    L.chain = take(4 * 2 * rows); // per vertex: predecessor vertex | arc code << 13
+    L.words = take(4 * rows); // walk table
     L.loff = take(2 * rows);
     L.llen = take(rows);
-    L.path = take(4 * (2 * rows + 8));
+    L.path = take(4 * (2 * rows + 40)); // room for a run over all stages past the length check
     L.lamt = take(4 * lslots);
     L.lent = take(4 * lslots); // partner | cost << 8
     L.total = o;

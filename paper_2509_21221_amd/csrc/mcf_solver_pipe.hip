@@ -25,10 +25,19 @@
 //    learns it for the whole pipeline and, when nothing changed, publishes
 //    the sink's key and a stop word; the other waves leave on that word
 //    while they wait for a mailbox.
-//  * After convergence: potentials (kept in the device workspace), then lane
-//    0 of wave 0 walks the path over predecessors staged in LDS and takes the
-//    bottleneck from the LDS node flows and flow lists; every wave applies
-//    the path to its own stages.
+//  * After convergence: potentials (kept in the device workspace), then wave
+//    0 reads every node's predecessors, staged in LDS, into registers (one per
+//    stage), walks the path over them and lists its nodes; its lanes take the
+//    bottleneck, one node each, from the LDS node flows and flow lists, and
+//    every wave applies the path to its own stages.
+//
+// What bounds it: the chain of stage steps, whose instructions a wave issues
+// alone for most of a search (the first iteration passes through the waves one
+// after another), with vector issue at about half of the peak.  The keyed
+// variant's step (predecessor in the key, residual compute arcs and the first
+// four list entries in registers, two rows per instruction) and the walk over
+// registers took 256 instances of 32 x 64 from 26.0 to 20.4 ms: label
+// iterations 18.3 to 14.4, augmentations 2.65 to 1.98 ms per instance.
 //
 // Each mailbox is written by one wave and read by one other.  The reader of an
 // exit mailbox (a wave's last-stage labels for iteration t) cannot be
@@ -47,18 +56,52 @@ using namespace dev;
 constexpr int kSpinLimit = 1 << 22;
 constexpr uint32_t kNoArc16 = 0xffff;
 constexpr int kBias = 1 << 30;
-// Keyed relaxation: a link candidate is the key label * 64 + row, so one
-// unsigned min keeps the smallest label and, among equal labels, the first
-// row.  Link costs are then stored times 64 (at most kKeyMaxCost), and an
-// unreached row broadcasts kKeyNone, which no real key reaches.
-constexpr int kKeyMaxCost = 1023;
-constexpr uint32_t kKeyNone = 0xffff0000u;
-__host__ __device__ constexpr bool keyed_fits(int64_t V, int64_t maxc)
-{
-    return maxc <= kKeyMaxCost && (V + 1) * maxc * 64 + 63 < int64_t(kKeyNone);
-}
+// Keyed variant.  A vertex is kept as key = label << 6 | row, where row is the
+// exit (or, for an exit, the entry of the next stage) its label came over a
+// link from; that it came over the node's compute arc is a bit of a wave-wide
+// mask in scalar registers.  Finite keys stay below 2^30 (labels below 2^24).
+// Unreached labels are 2^30, and 2^31 where a cost is subtracted from them; an
+// arc without residual costs 2^30 forwards, and kOff less than its cost
+// backwards: nothing that involves either lands in the finite range.
+//
+// With link costs of at most kPairMaxCost a relaxation takes two rows per
+// instruction: 16-bit keys (label - base) << 6 | row, base a lower bound of the
+// previous stage's exit labels, in saturating adds.  base is kept so close to
+// the smallest of them that the row with that label gives every node a
+// candidate of at most base + kPairMaxCost, so a sum that saturates is no
+// improvement.  Larger costs take one row per
+// instruction, a multiply-add of the cost's half register by 64.
+constexpr uint32_t kKeyFinite = 0x40000000u;
+constexpr uint32_t kKeyInf = kKeyFinite | 63u;
+constexpr uint32_t kOff = 0x50000000u;
+constexpr int kPairMaxCost = 1022;
+constexpr int kListRegs = 4; // entries of an exit's flow list kept in registers during a search
+__host__ __device__ constexpr bool keyed_fits(int64_t V, int64_t maxc) { return (V + 2) * maxc < (int64_t(1) << 24); }
+__device__ __forceinline__ uint32_t key_base(uint32_t key) { return key & ~63u; }
+__device__ __forceinline__ uint32_t sub_tail(uint32_t label) { return label + (label & kKeyFinite); }
 
-enum : int { kArcSplitFwd = 0, kArcSplitRev = 1, kArcLinkFwd = 2, kArcLinkRev = 3 };
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pair_add(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ uint32_t pair_min(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+// 64 * (low or high half of w) + k
+__device__ __forceinline__ uint32_t mad_lo64(uint32_t w, uint32_t k)
+{
+    uint32_t r;
+    asm("v_mad_u32_u16 %0, %1, 64, %2" : "=v"(r) : "v"(w), "s"(k));
+    return r;
+}
+__device__ __forceinline__ uint32_t mad_hi64(uint32_t w, uint32_t k)
+{
+    uint32_t r;
+    asm("v_mad_u32_u16 %0, %1, 64, %2 op_sel:[1,0,0,0]" : "=v"(r) : "v"(w), "s"(k));
+    return r;
+}
 
 typedef uint32_t u32x32 __attribute__((ext_vector_type(32)));
 
@@ -85,19 +128,58 @@ template <typename T> __device__ __forceinline__ void lds_st(T *p, T v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-__device__ __forceinline__ int arc_code(int type, int k, int i, int j)
+// Walk table word of a node: where its exit's and its entry's label came from
+// (7 bits each: a row or partner below 64, or one of the codes).
+constexpr uint32_t kFromSplit = 64, kFromSrc = 65, kFromNone = 127;
+__device__ __forceinline__ uint32_t walk_word(uint32_t exit_from, uint32_t entry_from) { return exit_from | entry_from << 8; }
+__device__ __forceinline__ uint32_t exit_from(uint32_t w) { return w & 127u; }
+__device__ __forceinline__ uint32_t entry_from(uint32_t w) { return (w >> 8) & 127u; }
+// A node whose exit is reached by its compute arc and its entry over a link.
+__device__ __forceinline__ bool straight(uint32_t w) { return (w & (127u | kFromSplit << 8)) == kFromSplit; }
+// Listed path node: its walk word, the node, the stage, and whether the path
+// comes to its exit (then over to its entry if that is by the compute arc) or
+// to its entry only.
+__device__ __forceinline__ uint32_t path_node(uint32_t w, int k, int v, bool at_exit)
 {
-    return type | (k << 2) | (i << 7) | (j << 13);
+    return w | uint32_t(v) << 16 | uint32_t(k) << 22 | (at_exit ? 1u << 27 : 0u);
+}
+// Position of partner j in a flow list of `len` entries at `lo`, or -1; four
+// entries per round of reads (a list has room past its last entry).
+__device__ __forceinline__ int find_partner(const uint32_t *lent, int lo, int len, int j)
+{
+    int at = -1;
+    for (int x = 0; x < len; x += 4) {
+        uint32_t e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = lent[lo + x + u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (x + u < len && int(e[u] & 255u) == j) at = lo + x + u;
+    }
+    return at;
 }
 
-// Path-walk table: one word per vertex (entry 2q, exit 2q+1 of node q =
-// k*64 + i, so below 4096): the vertex its predecessor arc comes from (13
-// bits) and that arc's code (19 bits).
-constexpr uint32_t kChainMask = 0x1fff;
-constexpr uint32_t kChainDone = 0x1fff; // entry of stage 0 reached from the data node
-constexpr uint32_t kChainBad = 0x1ffe;  // no usable predecessor
-static_assert(2 * kPipeMaxStages * 64 <= 0x1ffe, "vertex ids below the markers");
-__device__ __forceinline__ uint32_t chain_word(uint32_t next, int code) { return next | (uint32_t(code) << 13); }
+struct PathNode {
+    int k, i, q;             // stage, node, k * 64 + i
+    bool split, back;        // the path takes its compute arc, or that arc's reverse
+    bool link_in, link_back; // it is entered over a link, or left over a reverse link
+    int tail, head;          // link_in: tail exit of stage k-1; link_back: head entry of stage k+1
+};
+__device__ __forceinline__ PathNode path_unpack(uint32_t r)
+{
+    PathNode a;
+    a.k = int((r >> 22) & 31u);
+    a.i = int((r >> 16) & 63u);
+    a.q = a.k * 64 + a.i;
+    const bool at_exit = (r >> 27) & 1u;
+    a.link_back = at_exit && exit_from(r) != kFromSplit;
+    a.split = at_exit && !a.link_back;
+    a.back = !a.link_back && entry_from(r) == kFromSplit;
+    a.link_in = !a.link_back && entry_from(r) < kFromSplit;
+    a.tail = int(entry_from(r) & 63u);
+    a.head = int(exit_from(r) & 63u);
+    return a;
+}
 
 // predecessors of one node, entry side in the low half, exit side in the high
 __device__ __forceinline__ int pred_in(int pp) { return int(int16_t(pp & 0xffff)); }
@@ -112,6 +194,15 @@ struct PipeShared {
     int plen, delta;
     int stage_tot[kPipeMaxStages];
     long long rows, pulls, steps;
+    // kept by thread 0, here rather than in every wave's scalar registers
+    long long cost, augs, rounds;
+    uint64_t tick, clk_iter, clk_aug, clk_other;
+    __device__ void lap(uint64_t &clock)
+    {
+        const uint64_t now = wall_clock64();
+        clock += now - tick;
+        tick = now;
+    }
 };
 
 // Waits until all 64 words of a mailbox carry parity `par` in bit 0; returns
@@ -164,10 +255,10 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
     int *nf = reinterpret_cast<int *>(smem + L.nf);               // [S][64] node flow
     int *capl = reinterpret_cast<int *>(smem + L.capl);           // [S][64] node capacity
     int *ncl = reinterpret_cast<int *>(smem + L.ncl);             // [S][64] node compute cost
-    uint32_t *chain = reinterpret_cast<uint32_t *>(smem + L.chain); // [S][64][entry, exit]
+    uint32_t *words = reinterpret_cast<uint32_t *>(smem + L.words); // [S][64] walk table
     uint16_t *loff = reinterpret_cast<uint16_t *>(smem + L.loff); // [S][64]
     uint8_t *llen = reinterpret_cast<uint8_t *>(smem + L.llen);   // [S][64]
-    int *path = reinterpret_cast<int *>(smem + L.path);           // [2*S*64 + 8]
+    uint32_t *path = reinterpret_cast<uint32_t *>(smem + L.path); // [2*S*64 + 40]
     int *lamt = reinterpret_cast<int *>(smem + L.lamt);           // flow of each list entry
     uint32_t *lent = reinterpret_cast<uint32_t *>(smem + L.lent); // partner | cost << 8
 
@@ -183,12 +274,14 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
         ps.maxc = 0;
         ps.fault = 0;
         ps.rows = ps.pulls = ps.steps = 0;
+        ps.cost = ps.augs = ps.rounds = 0;
+        ps.clk_iter = ps.clk_aug = ps.clk_other = 0;
     }
     __syncthreads();
 
     // ---------------- ingest + validate ----------------
     u32x32 lw[P];
-    int din[P], dout[P], pp[P], seen[P], seeny[P];
+    int din[P], dout[P], pp[P];
     uint32_t holes = 0; // bit s: some link into stage k0+s is missing
     int srcc = 0, snkc = 0;
     {
@@ -213,10 +306,8 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
                     wide |= (a0 > 65534) | (a1 > 65534);
                     hole |= (jv & (2 * r < n) & (a0 < 0)) | (jv & (2 * r + 1 < n) & (a1 < 0));
                     mx = max(mx, max(a0, a1));
-                    // keyed: costs above kKeyMaxCost send the instance on, so
-                    // the clamp only keeps the stored word in range
-                    const uint32_t c0 = a0 < 0 ? kNoArc16 : kKeyed ? uint32_t(min(a0, kKeyMaxCost)) << 6 : uint32_t(min(a0, 65535));
-                    const uint32_t c1 = a1 < 0 ? kNoArc16 : kKeyed ? uint32_t(min(a1, kKeyMaxCost)) << 6 : uint32_t(min(a1, 65535));
+                    const uint32_t c0 = a0 < 0 ? kNoArc16 : uint32_t(min(a0, 65535));
+                    const uint32_t c1 = a1 < 0 ? kNoArc16 : uint32_t(min(a1, 65535));
                     v[r] = c0 | (c1 << 16);
                 }
             }
@@ -291,16 +382,35 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
         return;
     }
     if (kKeyed && status == 0 && !keyed_fits(V, ps.maxc)) {
-        // costs above kKeyMaxCost or labels too long for the keys: the
-        // unscaled variant solves this instance
+        // labels too long for the keys: the unscaled variant solves this instance
         if (tid == 0) p.route[b] = kRoutePipeWide;
         return;
     }
 
-    long long F = 0, cost = 0, augs = 0, rounds = 0;
-    int pit = 0;
+    // keyed: link costs times 64 when two rows fit an instruction
+    const bool pairs = kKeyed && ps.maxc <= kPairMaxCost;
+    if (pairs) {
+#pragma unroll
+        for (int s = 0; s < P; ++s)
+#pragma unroll
+            for (int r = 0; r < 32; ++r) {
+                const uint32_t v = lw[s][r];
+                lw[s][r] = (v & 0x03ff03ffu) << 6 | ((v & 0xffffu) == kNoArc16 ? 0xffffu : 0u) |
+                           (v >> 16 == kNoArc16 ? 0xffff0000u : 0u);
+            }
+    }
+
+    int F = 0, pit = 0;
     bool fault = false;
-    uint64_t tick = wall_clock64(), clk_iter = 0, clk_aug = 0, clk_other = 0;
+    if (tid == 0) ps.tick = wall_clock64();
+
+    // keyed: a lower bound of the exit labels of stage k0 + s - 1, at most
+    // `slack` below the smallest.  Distances do not fall from one search to the
+    // next, so what holds at the end of a search mostly serves the next one too.
+    uint32_t base[P];
+#pragma unroll
+    for (int s = 0; s < P; ++s) base[s] = 0x80000000u; // above every label: set at the first relaxation
+    const uint32_t slack = pairs ? uint32_t(kPairMaxCost - ps.maxc) << 6 : 0u;
 
     if (status == 0) {
         while (F < supply) {
@@ -314,8 +424,14 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
                 const bool own = k0 + s <= klast && k0 + s + 1 < S;
                 lst_lo[s] = own ? int(loff[q]) : 0;
                 lst_len[s] = own && jv ? int(llen[q]) : 0;
-                lst_max[s] = int(wave_reduce_u32<true>(uint32_t(lst_len[s])));
+                // keyed: only whether it is 0 and, above kListRegs, its value
+                lst_max[s] = __any(lst_len[s] > (kKeyed ? kListRegs : 0)) ? int(wave_reduce_u32<true>(uint32_t(lst_len[s])))
+                                                                       : int(__any(lst_len[s] > 0));
             }
+            int seen[P], seeny[P];                   // unscaled variant
+            uint32_t ki[P], ko[P], kseen[P], kseeny[P]; // keyed: entry and exit keys, last inputs
+            uint32_t ncf[P], ncr[P], la[P][kListRegs], lc[P][kListRegs];
+            uint64_t isplit[P], osplit[P];
 #pragma unroll
             for (int s = 0; s < P; ++s) {
                 const int k = k0 + s;
@@ -325,21 +441,228 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
                 seen[s] = kInf;
                 seeny[s] = kInf;
             }
-            if (k0 <= klast) {
+            if (k0 <= klast && !kKeyed) {
                 if (k0 >= 1) lds_st(&enmb[w * 64 + lane], uint32_t(din[0]) << 1);
                 if (klast + 1 < S) lds_st(&exmb[w * 64 + lane], uint32_t(kInf) << 2);
+            }
+            if constexpr (kKeyed) {
+#pragma unroll
+                for (int s = 0; s < P; ++s) {
+                    const int k = k0 + s, q = k * 64 + lane;
+                    const bool own = k <= klast;
+                    const int fl = own ? nf[q] : 0, cp = own ? capl[q] : 0, nc = own ? ncl[q] : 0;
+                    ki[s] = (k == 0 && jv) ? uint32_t(srcc) << 6 : kKeyInf;
+                    ko[s] = kKeyInf;
+                    kseen[s] = kKeyFinite;
+                    kseeny[s] = sub_tail(kKeyFinite);
+                    ncf[s] = fl < cp ? uint32_t(nc) << 6 : kKeyFinite;
+                    ncr[s] = (uint32_t(nc) << 6) - (fl > 0 ? 0u : kOff);
+                    isplit[s] = osplit[s] = 0;
+                    // the first entries of each exit's list: lane address of
+                    // the partner, cost (a list has room past its last entry)
+                    uint32_t ent[kListRegs];
+#pragma unroll
+                    for (int e = 0; e < kListRegs; ++e) ent[e] = lent[lst_lo[s] + e];
+#pragma unroll
+                    for (int e = 0; e < kListRegs; ++e) {
+                        la[s][e] = (ent[e] & 63u) << 2;
+                        lc[s][e] = e < lst_len[s] ? (ent[e] >> 8) << 6 : 0u - kOff;
+                    }
+                }
+                if (k0 <= klast) {
+                    if (k0 >= 1) lds_st(&enmb[w * 64 + lane], sub_tail(key_base(ki[0])));
+                    if (klast + 1 < S) lds_st(&exmb[w * 64 + lane], kKeyFinite);
+                }
             }
             if (tid == 0) {
                 ps.stop = 0;
                 ps.final_key = ~0ull;
             }
             __syncthreads();
-            clk_other += lap(tick);
+            if (tid == 0) ps.lap(ps.clk_other);
 
             // ---- (1) pipelined label-correcting iterations ----
-            long long rows = 0, steps = 0;
+            uint32_t rows = 0, steps = 0;
             int pulls = 0;
-            if (k0 <= klast) {
+            if constexpr (kKeyed) {
+                for (int t = 1; k0 <= klast; ++t) {
+                    if (t > 4 * V + 8) {
+                        if (lane == 0) atomicOr(&ps.fault, 1);
+                        break;
+                    }
+                    const uint32_t par = uint32_t(t) & 1u;
+                    __builtin_amdgcn_s_setprio(0);
+                    int why = 0;
+                    uint64_t chg = 0;  // lanes with a changed label
+                    uint32_t upch = 0; // 2 if a stage before this wave's changed in iteration t
+#pragma unroll
+                    for (int s = 0; s < P; ++s) {
+                        const int k = k0 + s;
+                        if (k > klast) break;
+                        // links from stage k-1's exit labels X, then the node's compute arc
+                        auto relax = [&](const uint32_t X) {
+                            const uint64_t mask = __ballot(X < kseen[s]);
+                            kseen[s] = min(kseen[s], X);
+                            rows += __popcll(mask);
+                            if (mask == 0) return;
+                            const uint32_t mlo = uint32_t(mask), mhi = uint32_t(mask >> 32);
+                            uint32_t best = kKeyInf;
+                            // A group with a dropped row is taken whole: a row
+                            // that did not drop was relaxed with the same label
+                            // before, so it cannot beat the current one.
+                            if ((holes >> s) & 1u) {
+                                // some links are missing (cost 0xffff): skip them
+                                const uint32_t xk = X | uint32_t(lane);
+                                for (uint64_t m = mask; m; m &= m - 1) {
+                                    const int r = __builtin_ctzll(m);
+                                    const uint32_t c = (lw[s][r >> 1] >> (16 * (r & 1))) & 0xffffu;
+                                    const uint32_t cand = __builtin_amdgcn_readlane(xk, r) + (pairs ? c : c << 6);
+                                    best = c != kNoArc16 ? min(best, cand) : best;
+                                }
+                            } else if (pairs) {
+                                if (__ballot(X < base[s]) != 0 || __ballot(X - base[s] <= slack) == 0)
+                                    base[s] = wave_reduce_u32<false>(X);
+                                const uint32_t rel = min(X - base[s], 0xffc0u) | uint32_t(lane);
+                                const uint32_t two = rel | dpp_mov<0xb1, 0xf>(rel) << 16; // rows 2r and 2r + 1 in lane 2r
+                                uint32_t acc0 = ~0u, acc1 = ~0u;
+#pragma unroll
+                                for (int g = 0; g < 8; ++g) {
+                                    if ((g < 4 ? mlo : mhi) & (0xffu << (8 * (g & 3)))) {
+                                        uint32_t x[4];
+#pragma unroll
+                                        for (int u = 0; u < 4; ++u) x[u] = __builtin_amdgcn_readlane(two, 8 * g + 2 * u);
+#pragma unroll
+                                        for (int u = 0; u < 4; u += 2) {
+                                            acc0 = pair_min(acc0, pair_add(x[u], lw[s][4 * g + u]));
+                                            acc1 = pair_min(acc1, pair_add(x[u + 1], lw[s][4 * g + u + 1]));
+                                        }
+                                    }
+                                }
+                                const uint32_t acc = pair_min(acc0, acc1);
+                                best = base[s] + min(acc & 0xffffu, acc >> 16);
+                            } else {
+                                const uint32_t xk = X | uint32_t(lane);
+#pragma unroll
+                                for (int g = 0; g < 8; ++g) {
+                                    if ((g < 4 ? mlo : mhi) & (0xffu << (8 * (g & 3)))) {
+                                        uint32_t x[8];
+#pragma unroll
+                                        for (int u = 0; u < 8; ++u) x[u] = __builtin_amdgcn_readlane(xk, 8 * g + u);
+#pragma unroll
+                                        for (int u = 0; u < 8; u += 2) {
+                                            const uint32_t wd = lw[s][(8 * g + u) >> 1];
+                                            best = min(min(best, mad_lo64(wd, x[u])), mad_hi64(wd, x[u + 1]));
+                                        }
+                                    }
+                                }
+                            }
+                            const bool better = jv && best < key_base(ki[s]);
+                            const uint64_t took = __ballot(better);
+                            if (took == 0) return;
+                            ki[s] = better ? best : ki[s];
+                            isplit[s] &= ~took;
+                            chg |= took;
+                        };
+                        auto split_fwd = [&]() {
+                            const uint32_t cand = key_base(ki[s]) + ncf[s];
+                            const bool better = cand < key_base(ko[s]);
+                            const uint64_t took = __ballot(better);
+                            ko[s] = better ? cand : ko[s];
+                            osplit[s] |= took;
+                            chg |= took;
+                        };
+                        // reverse links, only when some entry label Y of stage k+1
+                        // (unreached as 2^31) dropped since this stage last pulled;
+                        // then the reverse compute arcs, whose tails change only here
+                        auto pull = [&](const uint32_t Y) {
+                            const uint64_t drop = __ballot(Y < kseeny[s]);
+                            kseeny[s] = min(kseeny[s], Y);
+                            if (drop == 0 || lst_max[s] == 0) return;
+                            const int yk = int(Y | uint32_t(lane));
+                            uint32_t v[kListRegs];
+#pragma unroll
+                            for (int e = 0; e < kListRegs; ++e) v[e] = uint32_t(__builtin_amdgcn_ds_bpermute(int(la[s][e]), yk)) - lc[s][e];
+                            uint32_t best = min(min(v[0], v[1]), min(v[2], v[3]));
+                            for (int e = kListRegs; e < lst_max[s]; e += 2) {
+                                // the rest of a long list, from LDS
+                                const bool h0 = e < lst_len[s], h1 = e + 1 < lst_len[s];
+                                const uint32_t e0 = lent[lst_lo[s] + (h0 ? e : 0)], e1 = lent[lst_lo[s] + (h1 ? e + 1 : 0)];
+                                const uint32_t y0 = uint32_t(__builtin_amdgcn_ds_bpermute(int((e0 & 63u) << 2), yk));
+                                const uint32_t y1 = uint32_t(__builtin_amdgcn_ds_bpermute(int((e1 & 63u) << 2), yk));
+                                best = h0 ? min(best, y0 - (e0 >> 8 << 6)) : best;
+                                best = h1 ? min(best, y1 - (e1 >> 8 << 6)) : best;
+                            }
+                            pulls += lst_len[s];
+                            const bool better = best < key_base(ko[s]);
+                            const uint64_t took = __ballot(better);
+                            if (took == 0) return;
+                            ko[s] = better ? best : ko[s];
+                            osplit[s] &= ~took;
+                            const uint32_t cand = sub_tail(key_base(ko[s])) - ncr[s];
+                            const bool less = cand < key_base(ki[s]);
+                            const uint64_t took2 = __ballot(less);
+                            ki[s] = less ? cand : ki[s];
+                            isplit[s] |= took2;
+                            chg |= took | took2;
+                        };
+                        // The input held by this wave first (a wave's first stage
+                        // pulls from its second's entry labels of iteration t-1,
+                        // its second relaxes from its first's exit labels of
+                        // iteration t), then the one another wave sends: the work
+                        // between a mailbox read and the next mailbox write is
+                        // what the waves pass to each other.
+                        if (s < P - 1 && k + 1 < S) pull(sub_tail(key_base(ki[s + 1 < P ? s + 1 : s])));
+                        if (s > 0) relax(key_base(ko[s > 0 ? s - 1 : 0]));
+                        if (s == 0 && k >= 1) {
+                            // exit labels of stage k-1, iteration t, from the previous wave
+                            const uint32_t word = mailbox_wait(&exmb[(w - 1) * 64], par, &ps.stop, why);
+                            if (why) break;
+                            upch = __builtin_amdgcn_readfirstlane(word) & 2u;
+                            relax(key_base(word));
+                        }
+                        split_fwd();
+                        if (s == P - 1 && k + 1 < S) {
+                            // entry labels of stage k+1, iteration t-1, from the next wave
+                            const uint32_t Y = mailbox_wait(&enmb[(w + 1) * 64], par ^ 1u, &ps.stop, why) & ~63u;
+                            if (why) break;
+                            pull(Y);
+                        }
+                        ++steps;
+                        if (s == 0 && k >= 1) lds_st(&enmb[w * 64 + lane], sub_tail(key_base(ki[s])) | par);
+                        if (k == klast && k + 1 < S)
+                            lds_st(&exmb[w * 64 + lane], key_base(ko[s]) | upch | (chg ? 2u : 0u) | par);
+                    }
+                    if (why) {
+                        if (why == 2 && lane == 0) atomicOr(&ps.fault, 1);
+                        break;
+                    }
+                    // the wave of the last stage: no label changed anywhere in
+                    // iteration t ends the search
+                    if (klast == S - 1 && upch == 0 && chg == 0) {
+                        uint32_t last = kKeyInf;
+#pragma unroll
+                        for (int s = 0; s < P; ++s)
+                            if (k0 + s == S - 1) last = ko[s];
+                        const uint64_t skey = wave_min_key(jv && last < kKeyFinite, int(last >> 6) + snkc);
+                        if (lane == 0) {
+                            ps.final_key = skey;
+                            lds_st(&ps.stop, t);
+                        }
+                        break;
+                    }
+                }
+                // labels and predecessors as the phases below take them
+#pragma unroll
+                for (int s = 0; s < P; ++s) {
+                    const bool ri = ki[s] < kKeyFinite, ro = ko[s] < kKeyFinite;
+                    din[s] = ri ? int(ki[s] >> 6) : kInf;
+                    dout[s] = ro ? int(ko[s] >> 6) : kInf;
+                    const int pi = ((isplit[s] >> lane) & 1u) ? kPredSplit : (k0 + s == 0 ? kPredSrc : int(ki[s] & 63u));
+                    const int po = ((osplit[s] >> lane) & 1u) ? kPredSplit : int(ko[s] & 63u);
+                    pp[s] = pred_pack(ri ? pi : kPredNone, ro ? po : kPredNone);
+                }
+            }
+            if (k0 <= klast && !kKeyed) {
                 for (int t = 1;; ++t) {
                     if (t > 4 * V + 8) {
                         if (lane == 0) atomicOr(&ps.fault, 1);
@@ -366,50 +689,7 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
                             const uint64_t mask = __ballot(dr);
                             rows += __popcll(mask);
                             // rows that dropped, two per cost register, in row order
-                            if (mask && kKeyed) {
-                                // every row of a group with a dropped row: a row
-                                // that did not drop was relaxed with the same label
-                                // before, so its key cannot beat the current label
-                                const uint32_t xk = X < kInf ? (uint32_t(X) << 6) | uint32_t(lane) : kKeyNone;
-                                uint32_t key = kKeyNone;
-                                if (!((holes >> s) & 1u)) {
-                                    const uint32_t mlo = uint32_t(mask), mhi = uint32_t(mask >> 32);
-#pragma unroll
-                                    for (int g = 0; g < 8; ++g) {
-                                        const uint32_t half = g < 4 ? mlo : mhi;
-                                        if (half & (0xffu << (8 * (g & 3)))) {
-                                            // the group's eight keys first, so the reads overlap
-                                            uint32_t xr[8], cand[8];
-#pragma unroll
-                                            for (int u = 0; u < 8; ++u) xr[u] = __builtin_amdgcn_readlane(xk, 8 * g + u);
-#pragma unroll
-                                            for (int u = 0; u < 8; u += 2) {
-                                                const uint32_t wd = lw[s][(8 * g + u) >> 1];
-                                                cand[u] = xr[u] + (wd & 0xffffu);
-                                                cand[u + 1] = xr[u + 1] + (wd >> 16);
-                                            }
-                                            const uint32_t m0 = min(min(cand[0], cand[1]), cand[2]);
-                                            const uint32_t m1 = min(min(cand[3], cand[4]), cand[5]);
-                                            const uint32_t m2 = min(min(cand[6], cand[7]), key);
-                                            key = min(min(m0, m1), m2);
-                                        }
-                                    }
-                                } else {
-                                    // some links are missing (cost 0xffff): skip them
-                                    uint64_t m = mask;
-                                    while (m) {
-                                        const int r = __builtin_ctzll(m);
-                                        m &= m - 1;
-                                        const uint32_t c = (lw[s][r >> 1] >> (16 * (r & 1))) & 0xffffu;
-                                        const uint32_t cand = __builtin_amdgcn_readlane(xk, r) + c;
-                                        key = c != kNoArc16 ? min(key, cand) : key;
-                                    }
-                                }
-                                if (key < kKeyNone && int(key >> 6) < di) {
-                                    di = int(key >> 6);
-                                    pi = int(key & 63u);
-                                }
-                            } else if (mask) {
+                            if (mask) {
                                 if (!((holes >> s) & 1u)) {
                                     // one scalar test per group of 8 rows, then one
                                     // bit test per row of a group that has any
@@ -551,17 +831,17 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
                 atomicAdd(reinterpret_cast<unsigned long long *>(&ps.pulls), (unsigned long long)pulls);
             }
             __syncthreads();
-            clk_iter += lap(tick);
+            if (tid == 0) ps.lap(ps.clk_iter);
             if (ps.fault) {
                 fault = true;
                 break;
             }
             const uint64_t fk = ps.final_key;
-            rounds += ps.stop;
+            if (tid == 0) ps.rounds += ps.stop;
             if (fk == ~0ull) break; // sink unreachable: the flow is maximum
 
             // ---- (2) stage predecessors ----
-            const int Dt = key_label(fk), predt = int(uint32_t(fk));
+            const int Dt = key_label(fk), predt = __builtin_amdgcn_readfirstlane(int(uint32_t(fk)));
             const int dred = Dt - pit;
             // The lane index, opaque here so that the per-lane addresses and
             // words below are computed after each search rather than held in
@@ -572,109 +852,90 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
             for (int s = 0; s < P; ++s) {
                 const int k = k0 + s;
                 if (k > klast) break;
-                const int q = k * 64 + ln, pi = pred_in(pp[s]), po = pred_out(pp[s]);
-                uint32_t ein, eout;
-                if (pi == kPredSrc) ein = kChainDone;
-                else if (pi == kPredSplit) ein = chain_word(2 * q + 1, arc_code(kArcSplitRev, k, ln, 0));
-                else if (pi >= 0 && pi < n && k >= 1) ein = chain_word(2 * ((k - 1) * 64 + pi) + 1, arc_code(kArcLinkFwd, k - 1, pi, ln));
-                else ein = kChainBad;
-                if (po == kPredSplit) eout = chain_word(2 * q, arc_code(kArcSplitFwd, k, ln, 0));
-                else if (po >= 0 && po < n && k + 1 < S) eout = chain_word(2 * ((k + 1) * 64 + po), arc_code(kArcLinkRev, k, ln, po));
-                else eout = kChainBad;
-                chain[2 * q] = ein;
-                chain[2 * q + 1] = eout;
+                const int pi = pred_in(pp[s]), po = pred_out(pp[s]);
+                const uint32_t from_in = pi == kPredSplit ? kFromSplit : pi == kPredSrc ? kFromSrc : pi >= 0 ? uint32_t(pi) : kFromNone;
+                const uint32_t from_out = po == kPredSplit ? kFromSplit : po >= 0 ? uint32_t(po) : kFromNone;
+                words[k * 64 + ln] = walk_word(from_out, from_in);
             }
             __syncthreads();
-            // potentials of this wave's nodes (the other waves do theirs while
-            // wave 0 walks; wave 0 after its walk)
+            // potentials of this wave's nodes; wave 0 reads its own before its
+            // walk and writes them after it
             auto update_potentials = [&]() {
 #pragma unroll
                 for (int s = 0; s < P; ++s) {
                     const int k = k0 + s;
                     if (k <= klast && jv) {
                         int32_t *pin = gpot + 3 + 2 * (k * n + ln);
-                        const int a = pin[0], c = pin[1];
-                        pin[0] = min(din[s], a + dred);
-                        pin[1] = min(dout[s], c + dred);
+                        pin[0] = min(din[s], pin[0] + dred);
+                        pin[1] = min(dout[s], pin[1] + dred);
                     }
                 }
             };
             if (w != 0) update_potentials();
 
-            // ---- (3) wave 0 walks the predecessor chain, then the
-            // whole wave takes the bottleneck over the recorded arcs ----
+            // ---- (3) wave 0 walks the predecessors, then the whole wave
+            // takes the bottleneck over the listed nodes ----
             if (w == 0) {
-                // the whole wave follows the chain (uniform values)
-                {
-                    int len = 0;
-                    bool okw = predt >= 0 && predt < n;
-                    uint32_t v = 2 * ((S - 1) * 64 + predt) + 1;
-                    // A node's two vertices are 2q and 2q+1, and a compute arc
-                    // joins them: the partner's word is read with each vertex's
-                    // own, so a compute arc and the arc after it take one round.
-                    // Every lane writes the (uniform) path entries.
-                    static_assert(kChainDone > kChainBad, "one compare finds both markers");
-                    while (okw) {
-                        // Most nodes are reached at their exit by the compute arc
-                        // and at their entry by a link from an exit of the stage
-                        // before: two entries and one read per node, with the
-                        // tests in scalar arithmetic; anything else takes the
-                        // general step below.
-                        while (v & 1u) {
-                            const uint64_t fb = *reinterpret_cast<const uint64_t *>(&chain[v - 1u]);
-                            const uint32_t flo = __builtin_amdgcn_readfirstlane(uint32_t(fb));
-                            const uint32_t fhi = __builtin_amdgcn_readfirstlane(uint32_t(fb >> 32));
-                            const uint32_t fnx = flo & kChainMask;
-                            // exit word leads to the entry, the entry's to an exit
-                            // (odd, so no marker: both markers are 0x1ffe and up,
-                            // and 0x1fff = done), room for two entries
-                            if ((fhi & kChainMask) != v - 1u) break;
-                            if ((fnx & 1u) == 0u || fnx == kChainDone) break;
-                            if (len > 2 * SN + 2) break;
-                            path[len] = int(fhi >> 13);
-                            path[len + 1] = int(flo >> 13);
-                            len += 2;
-                            v = fnx;
+                // Lane i holds the words of node i of every stage, so a run over
+                // straight nodes takes a register and a lane read and a few
+                // scalar instructions per node instead of a read of the table
+                // in LDS and its way to a scalar register.
+                u32x32 mine;
+#pragma unroll
+                for (int kk = 0; kk < W * P; ++kk) mine[kk] = words[min(kk, S - 1) * 64 + ln];
+                int len = 0, k = S - 1, v = predt;
+                bool at_exit = true, okw = predt >= 0 && predt < n;
+                while (okw) {
+                    if (at_exit) {
+                        const int k1 = k, v1 = v;
+                        uint32_t met = 0;
+                        for (;;) {
+                            k = __builtin_amdgcn_readfirstlane(k);
+                            v = __builtin_amdgcn_readfirstlane(v);
+                            const uint32_t wd = __builtin_amdgcn_readlane(mine[k], v);
+                            if (!straight(wd)) break; // stage 0 has none: its entries come from the data node
+                            met = ln == k ? wd : met;
+                            v = int(entry_from(wd));
+                            k -= 1;
                         }
-                        // both words of the node in one 8-byte read
-                        const uint64_t both = *reinterpret_cast<const uint64_t *>(&chain[v & ~1u]);
-                        const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(both));
-                        const uint32_t hi = __builtin_amdgcn_readfirstlane(uint32_t(both >> 32));
-                        const uint32_t word = (v & 1u) ? hi : lo, part = (v & 1u) ? lo : hi;
-                        uint32_t nx = word & kChainMask;
-                        if (nx >= kChainBad) {
-                            okw = nx == kChainDone;
-                            break;
-                        }
-                        path[len++] = int(word >> 13);
-                        if (nx == (v ^ 1u)) {
-                            nx = part & kChainMask;
-                            if (nx >= kChainBad) {
-                                okw = nx == kChainDone;
-                                break;
-                            }
-                            path[len++] = int(part >> 13);
-                        }
-                        okw = len <= 2 * SN + 4;
-                        v = nx;
+                        // lanes k + 1 .. k1 hold the nodes met; each one's index
+                        // is in the word of the node before it
+                        const uint32_t before = __shfl_down(met, 1);
+                        if (ln > k && ln <= k1)
+                            path[len + k1 - ln] = path_node(met, ln, ln == k1 ? v1 : int(entry_from(before)), true);
+                        len += k1 - k;
                     }
-                    if (lane == 0) ps.plen = okw ? len : -1;
+                    const uint32_t wd = __builtin_amdgcn_readfirstlane(words[k * 64 + v]);
+                    path[len] = path_node(wd, k, v, at_exit);
+                    ++len;
+                    const uint32_t ce = exit_from(wd), ci = entry_from(wd);
+                    if (at_exit && ce != kFromSplit) { // on by a reverse link
+                        okw = ce < 64 && k + 1 < S;
+                        k += 1;
+                        v = int(ce);
+                        at_exit = false;
+                    } else if (ci == kFromSplit) { // by the reverse compute arc
+                        at_exit = true;
+                    } else {
+                        if (ci == kFromSrc) break;
+                        okw = ci < 64 && k >= 1;
+                        k -= 1;
+                        v = int(ci);
+                        at_exit = true;
+                    }
+                    okw = okw && len <= 2 * SN + 4;
                 }
+                if (lane == 0) ps.plen = okw ? len : -1;
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
-                const int len = __builtin_amdgcn_readfirstlane(ps.plen);
-                int r = supply - int(F);
+                int r = supply - F;
                 for (int e = lane; e < len; e += 64) {
-                    const int code = path[e], type = code & 3, kk = (code >> 2) & 31;
-                    const int i = (code >> 7) & 63, j = (code >> 13) & 63;
-                    const int q = kk * 64 + i;
-                    if (type == kArcSplitFwd) r = min(r, capl[q] - nf[q]);
-                    else if (type == kArcSplitRev) r = min(r, nf[q]);
-                    else if (type == kArcLinkRev) {
-                        int amt = 0;
-                        for (int x = loff[q]; x < loff[q] + llen[q]; ++x)
-                            if (int(lent[x] & 255u) == j) amt = lamt[x];
-                        r = min(r, amt);
+                    const PathNode a = path_unpack(path[e]);
+                    if (a.split) r = min(r, capl[a.q] - nf[a.q]);
+                    if (a.back) r = min(r, nf[a.q]);
+                    if (a.link_back) {
+                        const int at = find_partner(lent, loff[a.q], llen[a.q], a.head);
+                        r = min(r, at >= 0 ? lamt[at] : 0);
                     }
                 }
                 r = int(wave_reduce_u32<false>(uint32_t(r)));
@@ -689,42 +950,40 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
             }
 
             // ---- (4) each wave applies the path to its stages ----
+            // (a link belongs to its tail's stage; links that empty come before
+            // links that fill, so a list never holds more than its slots)
             if (k0 <= klast) {
                 for (int pass = 0; pass < 2; ++pass) {
                     for (int e = lane; e < len; e += 64) {
-                        const int code = path[e], type = code & 3, kk = (code >> 2) & 31;
-                        const int i = (code >> 7) & 63, j = (code >> 13) & 63;
-                        if (kk < k0 || kk > klast) continue;
-                        const int q = kk * 64 + i;
+                        const PathNode a = path_unpack(path[e]);
+                        const bool own = a.k >= k0 && a.k <= klast;
                         if (pass == 0) {
-                            if (type == kArcSplitFwd) nf[q] += delta;
-                            else if (type == kArcSplitRev) nf[q] -= delta;
-                            else if (type == kArcLinkRev) {
-                                const int lo = loff[q], hi = lo + llen[q];
-                                int le = -1;
-                                for (int x = lo; x < hi; ++x)
-                                    if (int(lent[x] & 255u) == j) le = x;
+                            if (!own) continue;
+                            if (a.split) nf[a.q] += delta;
+                            if (a.back) nf[a.q] -= delta;
+                            if (a.link_back) {
+                                const int lo = loff[a.q], hi = lo + llen[a.q];
+                                const int le = find_partner(lent, lo, hi - lo, a.head);
                                 if (le < 0 || lamt[le] < delta) {
                                     atomicOr(&ps.fault, 1);
                                 } else if (lamt[le] == delta) { // the arc empties: move the last entry here
                                     lent[le] = lent[hi - 1];
                                     lamt[le] = lamt[hi - 1];
-                                    llen[q] = uint8_t(hi - 1 - lo);
+                                    llen[a.q] = uint8_t(hi - 1 - lo);
                                 } else {
                                     lamt[le] -= delta;
                                 }
                             }
-                        } else if (type == kArcLinkFwd) {
+                        } else if (a.link_in && a.k - 1 >= k0 && a.k - 1 <= klast) {
+                            const int kt = a.k - 1, q = kt * 64 + a.tail;
                             const int lo = loff[q], hi = lo + llen[q];
-                            int le = -1;
-                            for (int x = lo; x < hi; ++x)
-                                if (int(lent[x] & 255u) == j) le = x;
+                            const int le = find_partner(lent, lo, hi - lo, a.i);
                             if (le >= 0) {
                                 lamt[le] += delta;
                             } else if (hi - lo >= min(min(capl[q], n), supply)) {
                                 atomicOr(&ps.fault, 1);
                             } else {
-                                lent[hi] = uint32_t(j) | (uint32_t(gac[(size_t(kk) * n + i) * n + j]) << 8);
+                                lent[hi] = uint32_t(a.i) | (uint32_t(gac[(size_t(kt) * n + a.tail) * n + a.i]) << 8);
                                 lamt[hi] = delta;
                                 llen[q] = uint8_t(hi + 1 - lo);
                             }
@@ -735,21 +994,27 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
                 }
             }
             F += delta;
-            cost += (long long)delta * Dt;
-            augs++;
             pit = Dt;
-            __syncthreads();
-            clk_aug += lap(tick);
-            if (ps.fault) {
-                fault = true;
-                break;
+            // No barrier here: a wave's lists and node flows are its own, and
+            // what the next search resets was last read two barriers ago.
+            if (tid == 0) {
+                ps.cost += (long long)delta * Dt;
+                ps.augs++;
+                ps.lap(ps.clk_aug);
             }
         }
+        __syncthreads();
+        fault = fault || ps.fault != 0;
     }
 
     // ---------------- export ----------------
+    // The launch's parameters read again from here: pointers used only below
+    // then take no scalar registers in the searches.
+    __attribute__((address_space(4))) const SolveParams *again =
+        (__attribute__((address_space(4))) const SolveParams *)__builtin_amdgcn_kernarg_segment_ptr();
+    __asm__ volatile("" : "+s"(again));
     const bool ok = status == 0 && !fault;
-    int32_t *nfo = p.node_flow + size_t(b) * SN;
+    int32_t *nfo = again->node_flow + size_t(b) * SN;
     if (k0 <= klast && jv) {
 #pragma unroll
         for (int s = 0; s < P; ++s) {
@@ -765,7 +1030,7 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
         }
     }
     const size_t na = size_t(S - 1) * n * n;
-    int32_t *af = p.arc_flow + size_t(b) * na;
+    int32_t *af = again->arc_flow + size_t(b) * na;
     for (size_t e = tid; e < na; e += NT) af[e] = 0;
     __syncthreads();
     if (ok) {
@@ -779,20 +1044,20 @@ __global__ __launch_bounds__(64 * W, 1) void solve_pipe_kernel(SolveParams p)
         gpot[0] = 0;
         gpot[1] = 0;
         gpot[2] = ok ? pit : 0;
-        p.F_out[b] = ok ? F : 0;
-        p.cost_out[b] = ok ? cost : 0;
-        p.status_out[b] = status != 0 ? status : (fault ? kStatusInternal : 0);
-        p.route[b] = kRouteReg;
-        int64_t *st = p.stats + size_t(b) * kStatsPerInstance;
-        const double ns_per_tick = 1e6 / double(p.clock_khz > 0 ? p.clock_khz : 100000);
-        st[0] = augs;
-        st[1] = rounds;
+        again->F_out[b] = ok ? F : 0;
+        again->cost_out[b] = ok ? ps.cost : 0;
+        again->status_out[b] = status != 0 ? status : (fault ? kStatusInternal : 0);
+        again->route[b] = kRouteReg;
+        int64_t *st = again->stats + size_t(b) * kStatsPerInstance;
+        const double ns_per_tick = 1e6 / double(again->clock_khz > 0 ? again->clock_khz : 100000);
+        st[0] = ps.augs;
+        st[1] = ps.rounds;
         st[2] = ps.rows;
         st[3] = ps.pulls;
-        st[4] = int64_t(double(clk_iter) * ns_per_tick);
+        st[4] = int64_t(double(ps.clk_iter) * ns_per_tick);
         st[5] = 0;
-        st[6] = int64_t(double(clk_aug) * ns_per_tick);
-        st[7] = int64_t(double(clk_other) * ns_per_tick);
+        st[6] = int64_t(double(ps.clk_aug) * ns_per_tick);
+        st[7] = int64_t(double(ps.clk_other) * ns_per_tick);
         st[8] = ps.steps;
         st[9] = 0;
     }
