@@ -137,6 +137,29 @@ def test_expand_bit_exact(S, n, m, slot, occupied, holes, with_src, first, count
     assert_same_batch(g, ref)
 
 
+@pytest.mark.parametrize("S,n,m,first,count", [
+    (8, 4, 5, 3, 2047), (8, 4, 5, 1, 2049), (8, 3, 6, 7, 8191), (8, 3, 6, 5, 20155),
+    (63, 2, 2, 1, 3905), (64, 2, 2, 0, 4032), (65, 2, 2, 3, 4157),
+])
+def test_expand_placements_per_workgroup(S, n, m, first, count):
+    """One to eight placements per workgroup, the last one partly filled, on
+    both sides of 64 stages; then the best placement of that many results."""
+    import torch
+
+    base, cands = _case(S, n, m, n - 1, False, 0.2, seed=S + n)
+    say("expand, several per workgroup", S, n, m, first, count)
+    g = gpu_whatif(base, n - 1, cands, first, count, solve=False, chunks=1)
+    assert_same_batch(g, OW.expand(base, n - 1, cands, first, count))
+    rng = np.random.default_rng(count)
+    F, cost, status = rng.integers(0, 3, count), rng.integers(0, count // 4, count), rng.integers(0, 2, count)
+    status[-1], F[-1], cost[-1] = 0, 2, 0 if count % 2 else count
+    order = sorted((-F[i], cost[i], i) for i in range(count) if status[i] == 0)[0]
+    with mcf.Solver(S, n, count) as s:
+        best = s.whatif_best(_t(F.astype(np.int64)), _t(cost.astype(np.int64)), _t(status.astype(np.int32)), first)
+        torch.cuda.synchronize()
+    assert tuple(int(x) for x in best.cpu().numpy()) == (first + order[2], -order[0], order[1])
+
+
 @pytest.mark.parametrize("S,n,m,slot,occupied,holes", [
     (2, 3, 2, 2, False, 0.0), (3, 4, 3, 0, False, 0.2), (4, 5, 3, 4, True, 0.1),
     (5, 6, 5, 5, False, 0.0), (4, 20, 4, 19, False, 0.0), (3, 70, 2, 69, False, 0.0),
