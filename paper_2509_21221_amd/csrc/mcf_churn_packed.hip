@@ -329,7 +329,7 @@ template <int G> __global__ __launch_bounds__(64, 2) void churn_packed_kernel(Ch
                     best = label_of(ks) + src5 + kCodeSrc;
                 } else {
                     if (!(new_out & (1u << (k - 1)))) return;
-                    best = exchange<G, false>(label_of(dout[k - 1]) | uint32_t(j), cin[k]);
+                    best = exchange<G, false, G>(label_of(dout[k - 1]) | uint32_t(j), cin[k]);
                 }
                 const bool better = j < n && best < label_of(din[k]);
                 if (!__any(better)) return;
@@ -366,7 +366,7 @@ template <int G> __global__ __launch_bounds__(64, 2) void churn_packed_kernel(Ch
                     constexpr int kn = k + 1 < MAXS ? k + 1 : k;
                     const uint32_t yr = sub_tail(label_of(din[kn])) | uint32_t(j);
                     if constexpr (XOR) {
-                        best = exchange<G, true>(yr, rc[k]);
+                        best = exchange<G, true, G>(yr, rc[k]);
                     } else {
                         uint32_t rem = k + 1 < S ? lmask[k * 64 + lane] : 0u;
                         best = ~0u;

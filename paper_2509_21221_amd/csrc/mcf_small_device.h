@@ -80,14 +80,15 @@ template <int G> __device__ __forceinline__ void turn(uint32_t (&c)[G])
 
 // min over the G lanes i of a group of (key of lane i) +- (cost of the link
 // between lane i and this lane)
-template <int G, bool SUB> __device__ __forceinline__ uint32_t exchange(uint32_t x, const uint32_t (&c)[G])
+template <int G, bool SUB, int ROWS> __device__ __forceinline__ uint32_t exchange(uint32_t x, const uint32_t (&c)[ROWS])
 {
-    static_assert(G == 4 || G == 8 || (G == 16 && !SUB), "group size");
-    uint32_t v[G];
+    static_assert(((G == 4 || G == 8) && ROWS == G) || (G == 16 && ROWS <= 16 && !SUB), "group size");
+    uint32_t v[ROWS];
     if constexpr (G == 16) {
-#define GWTF_ROW(I) v[I] = dpp<0x150 + I>(x) + c[I]
-        GWTF_ROW(0), GWTF_ROW(1), GWTF_ROW(2), GWTF_ROW(3), GWTF_ROW(4), GWTF_ROW(5), GWTF_ROW(6), GWTF_ROW(7);
-        GWTF_ROW(8), GWTF_ROW(9), GWTF_ROW(10), GWTF_ROW(11), GWTF_ROW(12), GWTF_ROW(13), GWTF_ROW(14), GWTF_ROW(15);
+#define GWTF_ROW(I)                                                                                                    \
+    if constexpr (I < ROWS) v[I % ROWS] = dpp<0x150 + I>(x) + c[I % ROWS]
+        GWTF_ROW(0); GWTF_ROW(1); GWTF_ROW(2); GWTF_ROW(3); GWTF_ROW(4); GWTF_ROW(5); GWTF_ROW(6); GWTF_ROW(7);
+        GWTF_ROW(8); GWTF_ROW(9); GWTF_ROW(10); GWTF_ROW(11); GWTF_ROW(12); GWTF_ROW(13); GWTF_ROW(14); GWTF_ROW(15);
 #undef GWTF_ROW
     } else {
         const uint32_t m = G == 8 ? dpp<kHalfMirror>(x) : 0u;
@@ -105,8 +106,8 @@ template <int G, bool SUB> __device__ __forceinline__ uint32_t exchange(uint32_t
     }
     uint32_t best = v[0];
 #pragma unroll
-    for (int i = 1; i + 1 < G; i += 2) best = min(min(best, v[i]), v[i + 1]);
-    return min(best, v[G - 1]);
+    for (int i = 1; i + 1 < ROWS; i += 2) best = min(min(best, v[i]), v[i + 1]);
+    return ROWS % 2 == 0 ? min(best, v[ROWS - 1]) : best;
 }
 
 // min / max / sum over the G lanes of a group, in every lane of the group

@@ -22,7 +22,8 @@
 //    a tree.
 //  * Forward relaxation.  The incoming link costs of a stage sit in vector
 //    registers (cost << 5, column j in lane j).  For G = 16 exit i's key
-//    reaches every lane through a DPP row broadcast fused into the add.  For
+//    reaches every lane through a DPP row broadcast fused into the add, for
+//    the first ROWS = 10, 13 or 16 exits.  For
 //    G = 4 and 8 the lanes exchange keys by XOR: register d of lane j holds
 //    the cost of the link from exit j ^ d, and the quad permutes (with one
 //    half-row mirror for d >= 4) deliver lane j ^ d's key inside the add, so
@@ -55,8 +56,8 @@
 // inputs and the flow export.  Measured against the form with row broadcasts,
 // node words read from LDS in every step and a recorded path (before / now):
 // 16,384 of 8 x 8 1,418 / 461 us, 1,024 of 4 x 4 135 / 59, one 8 x 8 494 /
-// 191, 40,320 of 8 x 13 with expansion 8.6 / 5.0 ms; 8,192 of 12 x 9 on one
-// wave per instance 27.5, here 3.5 ms with expansion.
+// 191, 40,320 of 8 x 13 with expansion 8.7 / 4.9 ms; 11,880 of 12 x 9 on one
+// wave per instance 27.5, here 3.4 ms with expansion.
 //
 // The first launch takes instances with supply <= 255 and costs <= 2047
 // (link flows in 8 bits).  The second (solve_small_rest_kernel) takes what
@@ -89,7 +90,7 @@ template <> struct CostType<true> { using type = uint32_t; };
 // on when WIDE).  Writes `route` for each instance it finishes and leaves
 // kRouteFallback for the others; true in the lanes of
 // the groups it left.
-template <int MAXS, int G, bool WIDE>
+template <int MAXS, int G, int ROWS, bool WIDE>
 __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t route_done, unsigned char *smem)
 {
     using Flow = typename FlowType<WIDE>::type;
@@ -120,7 +121,7 @@ __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t 
 
     // ---------------- ingest + validate ----------------
     int bad = supply < 0, mx = 0;
-    uint32_t cin[MAXS][G];             // cost << 5 of the links into node (k, j), k >= 1: from exit d (XOR: j ^ d)
+    uint32_t cin[MAXS][ROWS];             // cost << 5 of the links into node (k, j), k >= 1: from exit d (XOR: j ^ d)
     typename W::type nw[MAXS];         // the node's flow and capacity, as in its table word
     uint32_t nc5[MAXS];                // its compute cost << 5
     uint32_t value = uint32_t(max(supply, 0)); // bound on the flow value: the supply and every stage's capacity
@@ -139,15 +140,15 @@ __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t 
     each<MAXS - 1, false>([&](auto K) GWTF_INLINE {
         constexpr int k = K;
         if (k + 1 >= S) return;
-        int a[G];
+        int a[ROWS];
 #pragma unroll
-        for (int d = 0; d < G; ++d) {
+        for (int d = 0; d < ROWS; ++d) {
             // XOR: the links out of node j; G = 16: the links into it
             const int i = XOR ? j : d, jj = XOR ? j ^ d : j;
             a[d] = (node && i < n && jj < n) ? gac[k * nn + i * n + jj] : -1;
         }
 #pragma unroll
-        for (int d = 0; d < G; ++d) {
+        for (int d = 0; d < ROWS; ++d) {
             bad |= a[d] < -1;
             mx = max(mx, a[d]);
             const bool hole = a[d] < 0;
@@ -247,7 +248,7 @@ __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t 
                     if (!(new_out & kBegin)) return;
                 } else {
                     if (!(new_out & (1u << (k - 1)))) return;
-                    const uint32_t best = exchange<G, false>(label_of(dout[k - 1]) | uint32_t(j), cin[k]);
+                    const uint32_t best = exchange<G, false, ROWS>(label_of(dout[k - 1]) | uint32_t(j), cin[k]);
                     const bool better = best < label_of(din[k]);
                     rows_relaxed += n;
                     if (!__any(better)) return;
@@ -268,7 +269,7 @@ __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t 
                     const uint32_t yr = sub_tail(label_of(din[k + 1])) | uint32_t(j);
                     uint32_t best;
                     if constexpr (XOR) {
-                        best = exchange<G, true>(yr, rc[k]);
+                        best = exchange<G, true, G>(yr, rc[k]);
                         pulls += nn;
                     } else {
                         // links with flow out of this exit, two per pass
@@ -502,22 +503,22 @@ __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t 
     return inst && !mine;
 }
 
-template <int MAXS, int G>
+template <int MAXS, int G, int ROWS>
 __global__ __launch_bounds__(64, MAXS > 8 ? 1 : 2) void solve_small_kernel(SolveParams p, int R, int32_t route_done)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    solve_rows<MAXS, G, false>(p, R, route_done, smem);
+    solve_rows<MAXS, G, ROWS, false>(p, R, route_done, smem);
 }
 
 // Instances the first launch passed on: R at a time with wide values, then
 // what is left one after another.
-template <int MAXS, int G>
+template <int MAXS, int G, int ROWS>
 __global__ __launch_bounds__(64, MAXS > 8 ? 1 : 2) void solve_small_rest_kernel(SolveParams p, int R, int32_t route_done)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int first = blockIdx.x * R, lane = threadIdx.x;
     if (!__any(lane < R && first + lane < p.B && p.route[first + lane] == kRouteFallback)) return;
-    uint64_t left = __ballot(solve_rows<MAXS, G, true>(p, R, route_done, smem) && lane % G == 0);
+    uint64_t left = __ballot(solve_rows<MAXS, G, ROWS, true>(p, R, route_done, smem) && lane % G == 0);
     while (left) {
         const int r = __builtin_ctzll(left) / G;
         left &= left - 1;
@@ -526,13 +527,13 @@ __global__ __launch_bounds__(64, MAXS > 8 ? 1 : 2) void solve_small_rest_kernel(
     }
 }
 
-template <int MAXS, int G> hipError_t launch_stages(const SolveParams &p, size_t lds_max, hipStream_t s)
+template <int MAXS, int G, int ROWS> hipError_t launch_stages(const SolveParams &p, size_t lds_max, hipStream_t s)
 {
     const int S = p.S, n = p.n;
     const int R = rows_per_wave(64 / G, p.B);
     const size_t lds = small_layout<MAXS, G, false>(S, n, R).total;
     if (lds > lds_max) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((solve_small_kernel<MAXS, G>), dim3(unsigned((p.B + R - 1) / R)), dim3(64), lds, s, p, R,
+    hipLaunchKernelGGL((solve_small_kernel<MAXS, G, ROWS>), dim3(unsigned((p.B + R - 1) / R)), dim3(64), lds, s, p, R,
                        S <= kPackedStages ? kRouteSmall : kRouteLds);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -544,15 +545,15 @@ template <int MAXS, int G> hipError_t launch_stages(const SolveParams &p, size_t
     const size_t body = make_layout(S, n, q.list_slots, true).total + scratch_bytes(1, n);
     const size_t rest = std::max(small_layout<MAXS, G, true>(S, n, Rr).total, body);
     if (rest > lds_max) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((solve_small_rest_kernel<MAXS, G>), dim3(unsigned((p.B + Rr - 1) / Rr)), dim3(64), rest, s, q,
+    hipLaunchKernelGGL((solve_small_rest_kernel<MAXS, G, ROWS>), dim3(unsigned((p.B + Rr - 1) / Rr)), dim3(64), rest, s, q,
                        Rr, S <= kPackedStages ? kRouteGlobal : kRouteLds);
     return hipGetLastError();
 }
 
-template <int G> hipError_t launch_group(const SolveParams &p, size_t lds_max, hipStream_t s)
+template <int G, int ROWS> hipError_t launch_group(const SolveParams &p, size_t lds_max, hipStream_t s)
 {
-    return p.S <= kPackedStages ? launch_stages<kPackedStages, G>(p, lds_max, s)
-                                : launch_stages<kSmallMaxStages, G>(p, lds_max, s);
+    return p.S <= kPackedStages ? launch_stages<kPackedStages, G, ROWS>(p, lds_max, s)
+                                : launch_stages<kSmallMaxStages, G, ROWS>(p, lds_max, s);
 }
 
 } // namespace

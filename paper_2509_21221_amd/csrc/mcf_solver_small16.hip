@@ -1,8 +1,12 @@
-// The packed pass with 16 lanes per instance (mcf_small_kernel.h).
+// The packed pass for at most 16 nodes per stage, 16 lanes per instance
+// (mcf_small_kernel.h).
 #include "mcf_small_kernel.h"
 
 namespace gwtf {
 
-hipError_t launch_small_pass16(const SolveParams &p, size_t lds_max, hipStream_t s) { return launch_group<16>(p, lds_max, s); }
+hipError_t launch_small_pass16(const SolveParams &p, size_t lds_max, hipStream_t s)
+{
+    return launch_group<16, 16>(p, lds_max, s);
+}
 
 } // namespace gwtf

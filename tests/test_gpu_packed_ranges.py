@@ -68,6 +68,16 @@ def test_shapes_and_value_ranges(S, n):
     np.testing.assert_array_equal(g["passes"][ok], expected(batch)[ok])
 
 
+@pytest.mark.parametrize("S,n", [(5, 10), (3, 11), (11, 13), (8, 13), (4, 14), (9, 15)])
+def test_rows_of_a_relaxation(S, n):
+    """Node counts on both sides of the bounds (10, 13 and 16) at which a
+    relaxation takes fewer rows than the group has lanes, in each value range."""
+    batch = W.concat([W.random_small(9, S, n, seed=81 + i, cap_hi=9, cost_hi=cost, supply_hi=99, holes=0.2,
+                                     zero_cap=0.1) for i, cost in enumerate([2047, 20000, 1 << 20])])
+    print(f"packed rows S={S} n={n}", flush=True)
+    compare(batch, gpu_solve(batch))
+
+
 @pytest.mark.parametrize("S,n,B", [(3, 3, 1024), (3, 3, 1025), (3, 3, 16400), (5, 7, 8193), (4, 10, 4097),
                                    (12, 4, 2049), (10, 12, 1030)])
 def test_instances_per_wave(S, n, B):
