@@ -110,7 +110,7 @@ def valu_issue(kernel: str, config, kernel_s: float):
 
 
 KERNELS = {1: "solve_pipe_kernel", 2: "solve_kernel (LDS state)", 3: "solve_grid_kernel",
-           4: "solve_kernel (global-memory state)", 5: "solve_small_kernel (one to eight instances per wave)"}
+           4: "solve_kernel (global-memory state)", 5: "solve_small_kernel (one to sixteen instances per wave)"}
 PASS_LAUNCHES = {1: " (keyed launch per step; the unscaled launch after it has no instance and exits)",
                  3: " (one cooperative launch per instance)"}
 KERNEL_SYMBOLS = {1: "solve_pipe_kernel", 2: "solve_kernel_lds", 3: "solve_grid_kernel", 4: "solve_kernel_global",
@@ -299,15 +299,14 @@ def heuristic_counters():
 
 def heuristic_roofline(instance_rounds, kernel_ms, batch):
     """The heuristic simulation keeps each instance in LDS and issues vector
-    instructions back to back: rocprofv3 counts about 91 % of the VALU issue
-    peak on settings 1, 2 and 4.  Its roofline is that issue rate: VALU
+    instructions back to back.  Its roofline is that issue rate: VALU
     wave-instructions per launch (the committed counter record, which holds
     for the same sources, batch and seed) over the measured kernel time."""
     rec = heuristic_counters()
     total_s = sum(kernel_ms.values()) / 1e3
     line = {"bound": "alu", "unit": "VALU wave-instructions/s", "peak": VALU_ISSUE_PEAK,
             "achieved": None, "frac": None, "traffic": None,
-            "kernel": "heuristic_kernel (one launch per setting)", "kernel_ms": total_s * 1e3,
+            "kernel": "heuristic_kernel (one launch per setting, heuristic_general_kernel after it)", "kernel_ms": total_s * 1e3,
             "instance_rounds_per_s": instance_rounds / total_s}
     if rec is not None and batch == 16384:
         per = rec["per_setting"]
@@ -485,10 +484,9 @@ def run_churn(args):
     _, _, _, wk = solver.resolve_churn(*args_v, start, **costs, work=True)
     wk = wk.cpu().numpy()
     passes = solver.passes().cpu().numpy()
-    # The kernel is a chain of label-correcting rounds per instance (one
-    # workgroup barrier each) plus one lane's path and cycle walks, with the
-    # instance in LDS: bound by round latency, not by memory (its inputs are
-    # read once: inst_bytes per instance).
+    # The kernel is a chain of label-correcting rounds per instance, several
+    # instances per wave: bound by the dependent instructions of a round, not
+    # by memory (its inputs are read once: inst_bytes per instance).
     inst_bytes = 4 * (2 * S * n + (S - 1) * n * n + 2 * n + 1) + 20
     rounds_total = float(wk[:, 3].sum())
     line = {
@@ -509,9 +507,9 @@ def run_churn(args):
         "roofline": {"bound": "latency", "achieved": rounds_total / (warm_ms / 1e3),
                      "unit": "label-correcting rounds/s (all instances)", "peak": None, "frac": None,
                      "traffic": inst_bytes * B / (warm_ms / 1e3) / 1e9, "traffic_unit": "GB/s (inputs read once)",
-                     "kernel": "churn_kernel (one launch per step)",
-                     "note": "each round ends in a workgroup barrier and the walks are serial; the cold "
-                             "packed pass needs fewer label-correcting passes on this workload (cold_solve_ms)"},
+                     "kernel": "churn_packed_kernel (churn_kernel after it for what it passes on)",
+                     "note": "the cold packed pass needs fewer label-correcting passes on this workload "
+                             "(cold_solve_ms)"},
     }
     if args.cpu_budget > 0:
         line["cpu_baseline"] = cpu_baseline(var, args.cpu_budget, host_threads())

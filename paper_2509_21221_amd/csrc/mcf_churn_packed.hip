@@ -32,7 +32,7 @@
 // status and solved by the general form, launched right after.
 //
 // What bounds it: the dependent instructions of a search, as in the packed
-// pass, for about 25 searches per variant instead of its 17; a lone lane's
+// pass, for about 20 searches per variant instead of its 17; a lone lane's
 // walks and one instance per wave bounded the general form.  16,384 variants
 // of 8 x 8: 8.7 ms there, 1.29 ms here (75 rounds per variant; 285 there).
 #include "gwtf_mcf.h"

@@ -1,4 +1,4 @@
-// Internal interface of the packed small-instance pass (mcf_solver_small.hip):
+// Internal interface of the packed small-instance pass (mcf_small_kernel.h):
 // one to sixteen instances per wave, for at most 16 stages of at most 16
 // nodes.  Not part of the public C ABI.
 #pragma once

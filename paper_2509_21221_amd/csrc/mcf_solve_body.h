@@ -1,6 +1,6 @@
 // The general solver of one instance by one workgroup, shared by the LDS and
 // fallback passes (mcf_solver.hip) and the packed pass's rest launch
-// (mcf_solver_small.hip).
+// (mcf_small_kernel.h).
 //
 // Method (paper Sec. V-A, Eq. 2 objective): successive shortest paths with
 // Johnson potentials.  Each instance is owned by one workgroup, which runs

@@ -33,7 +33,7 @@
 //
 // What bounds it: the chain of stage steps, whose instructions a wave issues
 // alone for most of a search (the first iteration passes through the waves one
-// after another), with vector issue at about half of the peak.  The keyed
+// after another), with vector issue at 0.35 of the peak.  The keyed
 // variant's step (predecessor in the key, residual compute arcs and the first
 // four list entries in registers, two rows per instruction) and the walk over
 // registers took 256 instances of 32 x 64 from 26.0 to 20.4 ms: label
