@@ -305,7 +305,8 @@ template <bool kLocated> __global__ __launch_bounds__(kGridThreads, 1) void solv
     const int S = p.S, n = p.n, SN = S * n, V = 2 * SN + 3;
     const int g = int(blockIdx.x) - li * nbi, k = g / gp.slices, s = g % gp.slices;
     const int j0 = s * kGridNB, nown = min(kGridNB, n - j0);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // scalar, so that tests on it are
     // rows of the previous stage rounded up to whole groups of 32 (the link
     // sweep reads four rows at a time in each of eight lane groups)
     const int npad = (n + 31) & ~31;
@@ -664,8 +665,8 @@ template <bool kLocated> __global__ __launch_bounds__(kGridThreads, 1) void solv
                     sh_key = ~0ull;
                     sh_changed = 0;
                 }
-                int s0 = ld(&ctrl[kCtlStop]);
-                uint32_t a0 = ld(&ex_f[wi]), c0 = ld(&en_b[wi]);
+                int s0 = ld(&ctrl[kCtlStop]), s1 = 0;
+                uint32_t a0 = ld(&ex_f[wi]), c0 = ld(&en_b[wi]), a1 = 0, c1 = 0;
                 // The sink's label so far bounds which changes matter: a vertex
                 // whose reduced label reaches the sink's cannot lie on a
                 // shortest path to it, and its label is only an upper bound,
@@ -674,8 +675,9 @@ template <bool kLocated> __global__ __launch_bounds__(kGridThreads, 1) void solv
                 const unsigned long long sbest = ld(sinkbest_w);
                 for (int spins = 0;; spins += 2) {
                     __builtin_amdgcn_s_sleep(1);
-                    const int s1 = ld(&ctrl[kCtlStop]);
-                    const uint32_t a1 = ld(&ex_f[wi]), c1 = ld(&en_b[wi]);
+                    s1 = ld(&ctrl[kCtlStop]);
+                    a1 = ld(&ex_f[wi]);
+                    c1 = ld(&en_b[wi]);
                     if (take(a0, c0, s0, spins)) break;
                     __builtin_amdgcn_s_sleep(1);
                     s0 = ld(&ctrl[kCtlStop]);
@@ -908,6 +910,11 @@ template <bool kLocated> __global__ __launch_bounds__(kGridThreads, 1) void solv
                     if (gq == 0) my_pulls += r_len;
                 }
                 if (has_next && pull) pk = row_group_min(pk);
+
+                // The reads that were still in flight when the wait above ended keep
+                // their registers up to here; reused earlier, they would hold the
+                // wave up until they are back (64 x 512: 907 ms, now 895).
+                asm volatile("" ::"v"(a0), "v"(a1), "v"(c0), "v"(c1), "v"(s0), "v"(s1));
 
                 // compute arcs of the owned nodes (group 0 of each column)
                 bool sink_has = false;
