@@ -27,8 +27,12 @@ def hipcc() -> str:
 
 # Per-source backend options.  The grid pass is scheduled for memory clauses
 # (2 % faster on the 64 x 512 instance); the register pass is not (the same
-# strategy spills three more registers there for no gain).
-EXTRA_FLAGS = {"mcf_solver_grid.hip": ["-mllvm", "-amdgpu-sched-strategy=max-memory-clause"]}
+# strategy spills three more registers there for no gain).  Its atomics are
+# issued by one lane already; combined over a wave, the arrival of an iteration
+# would be waited for before the next iteration's first reads go out (64 x 512
+# 855 -> 839 ms, four located 16 x 200 18.2 -> 17.8 ms).
+EXTRA_FLAGS = {"mcf_solver_grid.hip": ["-mllvm", "-amdgpu-sched-strategy=max-memory-clause",
+                                       "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
 
 
 def build(verbose: bool = False) -> str:
