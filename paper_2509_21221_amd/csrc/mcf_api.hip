@@ -278,7 +278,7 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
     const int waves = lds_waves(n);
     const int64_t slots = pipe_slots > 0 ? 0 : lds_slots(S, n, waves, d.lds_max);
     if (small_pass_fits(S, n)) {
-        // Up to sixteen instances per wave; a second launch solves those
+        // Up to sixteen instances per wave; the launches after it solve those
         // outside the first one's bounds, so no fallback pass follows.
         p.list_slots = 0;
         p.route_all = 0;
@@ -323,9 +323,10 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
         need_fallback = true;
     } else if (slots > 0) {
         p.list_slots = slots;
-        p.route_all = 0;
+        p.route_all = 1;
         size_t lds = make_layout(S, n, slots, true).total + scratch_bytes(waves, n);
         if ((e = launch_lds_pass(p, waves, lds, stream)) != hipSuccess) return {GWTF_ERR_DEVICE, "LDS solver launch", e};
+        p.route_all = 0;
         // Worst-case list demand of an instance: (S-1) * n * min(n, cap, supply).
         need_fallback = slots < worst;
     } else {

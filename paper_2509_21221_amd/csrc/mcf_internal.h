@@ -35,7 +35,7 @@ struct SolveParams {
     unsigned char *state; // fallback pass: per-instance state, state_stride bytes each
     size_t state_stride;
     int64_t list_slots;   // flow-list capacity of one instance
-    int32_t route_all;    // fallback pass: solve every instance, ignoring route[]
+    int32_t route_all;    // LDS and fallback passes: solve every instance, ignoring route[]
     int32_t clock_khz;    // device wall-clock rate, for the phase timers
 };
 

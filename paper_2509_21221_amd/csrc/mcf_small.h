@@ -10,7 +10,7 @@ namespace gwtf {
 constexpr int kPackedStages = 8;    // reported as the packed pass (and its rest as the fallback)
 constexpr int kSmallMaxStages = 16; // deeper pipelines up to here are reported as the LDS pass
 inline bool small_pass_fits(int S, int n) { return S >= 1 && S <= kSmallMaxStages && n <= 16; }
-// Both launches of the pass, for n at most the number in the name: 4 and 8
+// The launches of the pass, for n at most the number in the name: 4 and 8
 // lanes per instance, then 16 with a relaxation over that many rows.  With all
 // 16 rows 11,880 instances of 12 x 9 took 3.88 ms and 40,320 of 8 x 13 4.95 ms,
 // with 10 and 13 rows 3.63 and 4.87 ms.  They finish every instance of the batch.

@@ -63,7 +63,8 @@
 // (link flows in 8 bits).  The second (solve_small_rest_kernel) takes what
 // that one passed on, in the same way with 16-bit flows while labels stay
 // below 2^25 and the value below 2^16, and one instance per wave by the
-// general method (mcf_solve_body.h) beyond that; its workgroups leave at once
+// general method (mcf_solve_body.h) beyond that, in a third launch for large
+// batches of more than 8 stages (launch_stages); its workgroups leave at once
 // when there is nothing to do (5 us for 16,384 instances).  A workgroup of 16
 // waves per instance with its state in device memory took 42.0 ms for 4,096
 // instances of 8 x 5 with supplies above 255 (now 0.37) and 26.8 ms for 1,500
@@ -510,16 +511,17 @@ __global__ __launch_bounds__(64, MAXS > 8 ? 1 : 2) void solve_small_kernel(Solve
     solve_rows<MAXS, G, ROWS, false>(p, R, route_done, smem);
 }
 
-// Instances the first launch passed on: R at a time with wide values, then
-// what is left one after another.
+// Instances the first launch passed on: R at a time with wide values, then,
+// when `general`, what is left one after another.
 template <int MAXS, int G, int ROWS>
-__global__ __launch_bounds__(64, MAXS > 8 ? 1 : 2) void solve_small_rest_kernel(SolveParams p, int R, int32_t route_done)
+__global__ __launch_bounds__(64, MAXS > 8 ? 1 : 2) void solve_small_rest_kernel(SolveParams p, int R, int32_t route_done,
+                                                                                 bool general)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int first = blockIdx.x * R, lane = threadIdx.x;
     if (!__any(lane < R && first + lane < p.B && p.route[first + lane] == kRouteFallback)) return;
     uint64_t left = __ballot(solve_rows<MAXS, G, ROWS, true>(p, R, route_done, smem) && lane % G == 0);
-    while (left) {
+    while (general && left) {
         const int r = __builtin_ctzll(left) / G;
         left &= left - 1;
         __syncthreads();
@@ -543,11 +545,24 @@ template <int MAXS, int G, int ROWS> hipError_t launch_stages(const SolveParams 
     SolveParams q = p;
     q.list_slots = int64_t(S > 1 ? S - 1 : 0) * n * n; // lists of the worst case: at most 3840 entries
     const size_t body = make_layout(S, n, q.list_slots, true).total + scratch_bytes(1, n);
-    const size_t rest = std::max(small_layout<MAXS, G, true>(S, n, Rr).total, body);
-    if (rest > lds_max) return hipErrorInvalidValue;
+    // With more than 8 stages the rest kernel's registers let one wave run per
+    // SIMD, a lean workgroup's let as many as its LDS allows: what the wide form
+    // leaves goes to a launch of its own once a wave would hold several of them
+    // (costs around half a million, 16,384 instances of 9 x 4: 13.1 ms within
+    // the rest launch, 4.1 in their own; 4,096 of 12 x 9: 35.0 and 15.4; 16,384 of
+    // 16 x 4: 27.0 and 8.4).  Where it finds nothing to do that launch costs 2 us
+    // for 4,096 instances and 5 for 16,384.
+    // One instance per wave takes as long in either (12 x 9: 3.8 ms alone, 9.4
+    // for 256), and with at most 8 stages the rest launch is the faster way than
+    // the fallback pass's workgroup of 16 waves (one 8 x 8 1.7 against 2.6 ms,
+    // 16,384 of them 41 against 242 ms).
+    const bool general = S <= kPackedStages || R == 1;
+    const size_t rows = small_layout<MAXS, G, true>(S, n, Rr).total, rest = general ? std::max(rows, body) : rows;
+    if (rows > lds_max || body > lds_max) return hipErrorInvalidValue;
     hipLaunchKernelGGL((solve_small_rest_kernel<MAXS, G, ROWS>), dim3(unsigned((p.B + Rr - 1) / Rr)), dim3(64), rest, s, q,
-                       Rr, S <= kPackedStages ? kRouteGlobal : kRouteLds);
-    return hipGetLastError();
+                       Rr, S <= kPackedStages ? kRouteGlobal : kRouteLds, general);
+    if ((e = hipGetLastError()) != hipSuccess || general) return e;
+    return launch_lds_pass(q, 1, body, s);
 }
 
 template <int G, int ROWS> hipError_t launch_group(const SolveParams &p, size_t lds_max, hipStream_t s)

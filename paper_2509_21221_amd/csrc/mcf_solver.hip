@@ -8,14 +8,15 @@ namespace {
 
 using namespace dev;
 
-// One workgroup per instance: narrow state in LDS (n <= 64), or wide state
-// in device memory for the instances the other passes handed on.
+// One workgroup per instance, or per instance the passes before handed on
+// (route_all tells): narrow state in LDS (n <= 64), or wide state in device
+// memory.
 template <int WAVES, bool NARROW>
 __global__ __launch_bounds__(WAVES * 64) void solve_kernel(SolveParams p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int b = blockIdx.x;
-    if (!NARROW && !p.route_all && p.route[b] != kRouteFallback) return;
+    if (!p.route_all && p.route[b] != kRouteFallback) return;
     solve_body<WAVES, NARROW>(p, b, NARROW ? kRouteLds : kRouteGlobal, smem);
 }
 

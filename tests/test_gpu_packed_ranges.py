@@ -89,6 +89,32 @@ def test_instances_per_wave(S, n, B):
     compare(batch, gpu_solve(batch))
 
 
+@pytest.mark.parametrize("S,n,B", [(9, 4, 1024), (9, 4, 1025), (16, 16, 1026), (12, 9, 2051), (16, 3, 4100)])
+def test_deep_instances_beyond_the_wide_form(S, n, B):
+    """More than 8 stages with costs beyond the 16-bit form, alone in their
+    waves (up to 1,024 instances) and in a launch of their own, where every
+    third, none and nearly all of a wave's instances are passed on.  The general
+    method alone reports the time of the backward sweeps apart."""
+    most = (1 << 27) // (2 * S * n + 3)  # labels up to 2^27
+    far = W.random_small(B, S, n, seed=63, cap_hi=5, cost_hi=most, supply_hi=9, holes=0.1, zero_cap=0.1)
+    far.node_cost[:, 0, 0] = most
+    near = W.random_small(B, S, n, seed=64, cap_hi=5, cost_hi=900, supply_hi=9, holes=0.1, zero_cap=0.1)
+    near.supply[1::5] = 300
+    third = np.arange(B) % 3 == 0
+    third[B // 2:] = np.arange(B - B // 2) % 67 != 5
+    third[B // 3:B // 2] = False
+    for key in ("node_cap", "node_cost", "arc_cost", "src_cost", "snk_cost", "supply"):
+        getattr(near, key)[third] = getattr(far, key)[third]
+    near.supply[:] = np.maximum(near.supply, 2)
+    print(f"packed deep leftovers S={S} n={n} B={B}", flush=True)
+    g = gpu_solve(near, stats=True)
+    compare(near, g)
+    ok = g["status"] == 0
+    assert (g["passes"][ok] == mcf.GWTF_PASS_LDS).all()
+    several = ok & (g["stats"][:, 0] > 1)  # a second search sweeps backwards
+    np.testing.assert_array_equal((g["stats"][:, 5] > 0)[several], third[several])
+
+
 def zigzag(S, n):
     """Two unit chains a and d that the first two paths take; the third must
     enter at b, run back along a, over to c, back along d and out through e:
