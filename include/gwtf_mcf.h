@@ -123,7 +123,9 @@ gwtf_status_t gwtf_mcf_get_flows(gwtf_mcf_t *h, int32_t first, int32_t count,
  * potential update, and the rest (label reset, sink update), then the
  * executed forward and backward layer steps (0 where not tracked).  The
  * register pass and the passes with several instances per wave report both
- * sweeps in the first of the four clocks, those of the instance's wave.  For
+ * sweeps in the first of the four clocks.  With several instances per wave the
+ * clocks and the rounds and relaxations are those made until the whole wave is
+ * done (relaxations over the instance's own rows and links with flow).  For
  * instances of the grid pass (GWTF_PASS_GRID) the clocks are workgroup 0's:
  * label iterations, then 0, then the potential update with the path walks
  * and augmentations of a search (tied exits included), then the rest (label

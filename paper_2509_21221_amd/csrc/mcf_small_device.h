@@ -133,7 +133,9 @@ template <int G> __device__ __forceinline__ uint32_t group_sum(uint32_t v)
 }
 
 // Walk table word of a node: entry code, exit code << 5, then its flow and
-// capacity (8 bits each, 16 when WIDE).
+// capacity (8 bits each, 16 when WIDE); for G < 16 also, in the top four bits of
+// the low half, the number of links with flow out of it.
+constexpr int kLinksAt = 28;
 template <bool WIDE> struct Word {
     using type = uint32_t;
     static constexpr int flow = 10, cap = 18;
@@ -174,8 +176,6 @@ template <int MAXS, int G, bool WIDE> __host__ __device__ inline SmallLayout sma
     L.total = o;
     return L;
 }
-
-// Converged groups wait for this many of the wave (or all that search).
 
 __device__ __forceinline__ int opaque_s(int x)
 {

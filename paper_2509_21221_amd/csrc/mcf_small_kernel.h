@@ -76,6 +76,7 @@
 #include "mcf_small.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace gwtf {
 namespace {
@@ -192,7 +193,10 @@ __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t 
     // ---------------- successive shortest paths ----------------
     const int goal = int(value); // no flow has a larger value
     int F = 0, augs = 0, rounds = 0;
-    long long cost = 0, rows_relaxed = 0, pulls = 0;
+    long long cost = 0, rows_relaxed = 0;
+    // reverse-link relaxations of this lane: at most 65,535 searches of 259
+    // rounds over 15 * 8 links for G < 16
+    std::conditional_t<XOR, uint32_t, uint64_t> pulls = 0;
     uint32_t pit = 0; // the sink's potential, << 5 as all labels here
     bool active = mine && status == 0 && goal > 0; // this group still searches
     uint64_t tick = wall_clock64(), clk_label = 0, clk_aug = 0;
@@ -271,7 +275,9 @@ __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t 
                     uint32_t best;
                     if constexpr (XOR) {
                         best = exchange<G, true, G>(yr, rc[k]);
-                        pulls += nn;
+                        // links with flow out of the exit: its word's top four
+                        // bits, in one instruction
+                        pulls = __builtin_amdgcn_udot8(uint32_t(nw[k]), 1u << kLinksAt, pulls, false);
                     } else {
                         // links with flow out of this exit, two per pass
                         uint32_t rem = lmask[k * 64 + lane];
@@ -435,6 +441,8 @@ __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t 
                     if (had == (via ? delta : 0u)) { // the link empties or begins to carry flow
                         if constexpr (XOR) {
                             atomicAdd(&rcost[ridx(lk, gb + tail, tail ^ head)], via ? 0u - kOff : kOff);
+                            atomicAdd(reinterpret_cast<uint32_t *>(&table[lk * 64 + gb + tail]),
+                                      via ? 0u - (1u << kLinksAt) : 1u << kLinksAt);
                         } else {
                             uint32_t *mask = &lmask[lk * 64 + gb + tail];
                             if (via) atomicAnd(mask, ~(1u << head));
@@ -461,7 +469,8 @@ __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t 
     }
 
     // ---------------- export ----------------
-    if constexpr (!XOR) pulls = (long long)group_sum<G>(uint32_t(pulls));
+    uint64_t all_pulls = pulls;
+    for (int o = G / 2; o > 0; o >>= 1) all_pulls += __shfl_xor(all_pulls, o);
     if (mine) {
         const bool ok = status == 0;
         const size_t na = size_t(S > 1 ? S - 1 : 0) * nn;
@@ -491,7 +500,7 @@ __device__ __forceinline__ bool solve_rows(const SolveParams &p, int R, int32_t 
             s[0] = augs;
             s[1] = rounds;
             s[2] = rows_relaxed;
-            s[3] = pulls;
+            s[3] = int64_t(all_pulls);
             const double ns_per_tick = 1e6 / double(p.clock_khz > 0 ? p.clock_khz : 100000);
             s[4] = int64_t(double(clk_label) * ns_per_tick); // both sweeps
             s[5] = 0;

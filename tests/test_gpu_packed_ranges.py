@@ -115,6 +115,31 @@ def test_deep_instances_beyond_the_wide_form(S, n, B):
     np.testing.assert_array_equal((g["stats"][:, 5] > 0)[several], third[several])
 
 
+@pytest.mark.parametrize("S,n,wide", [(8, 8, False), (5, 7, False), (8, 4, False), (12, 8, False), (8, 8, True)])
+def test_reverse_link_counter(S, n, wide):
+    """The counter of reverse-link relaxations counts links that carry flow: no
+    more than one per stage and round while one unit path is in the flow, and
+    the same number whether the instance has a group of its own width or, with
+    absent nodes added, 16 lanes (the same searches, round by round)."""
+    x = W.random_small(1, S, n, seed=65, cap_hi=3, cost_hi=200, supply_hi=9)
+    x.supply[:] = 256 + 40 if wide else 40
+    two = x.instance(0)
+    two.node_cap[:] = np.minimum(two.node_cap, 1)
+    two.supply[:] = 2
+    padded = W.random_small(1, S, 9, seed=1)
+    padded.node_cap[:] = 0
+    padded.arc_cost[:] = W.NO_ARC
+    for key in ("node_cap", "node_cost", "src_cost", "snk_cost"):
+        getattr(padded, key)[..., :n] = getattr(x, key)
+    padded.arc_cost[..., :n, :n] = x.arc_cost
+    padded.supply[:] = x.supply
+    print(f"packed counters S={S} n={n} wide={wide}", flush=True)
+    a, b, c = (gpu_solve(y, stats=True)["stats"][0] for y in (x, padded, two))
+    np.testing.assert_array_equal(a[:2], b[:2])
+    assert a[0] > 1 and a[3] == b[3] > 0
+    assert c[0] == 2 and 0 < c[3] <= (S - 1) * c[1]
+
+
 def zigzag(S, n):
     """Two unit chains a and d that the first two paths take; the third must
     enter at b, run back along a, over to c, back along d and out through e:
