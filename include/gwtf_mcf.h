@@ -89,8 +89,8 @@ typedef struct {
 
 /* Creates a solver for batches of `shape` on shape->device, enqueueing on
  * `hip_stream` (a hipStream_t; NULL = the device's null stream).  Allocates
- * the workspace (flows, potentials, fallback state) for shape->max_batch
- * instances.  *out receives the handle, or NULL on failure. */
+ * the workspace (flows, potentials, and for shapes outside S <= 16, n <= 16 the
+ * fallback state) for shape->max_batch instances.  *out receives the handle, or NULL on failure. */
 gwtf_status_t gwtf_mcf_create(const gwtf_mcf_shape_t *shape, void *hip_stream, gwtf_mcf_t **out);
 
 /* Solves every instance of the batch (paper Eq. 2 optimum per instance).

@@ -140,6 +140,21 @@ def test_reverse_link_counter(S, n, wide):
     assert c[0] == 2 and 0 < c[3] <= (S - 1) * c[1]
 
 
+@pytest.mark.parametrize("S,n,B", [(8, 13, 40320), (16, 16, 4096)])
+def test_workspace_without_fallback_state(S, n, B):
+    """A handle of a shape that the packed pass finishes holds the flows,
+    potentials and counters of its instances and little else."""
+    import torch
+
+    each = 4 * (1 + S * n + (S - 1) * n * n + 2 * S * n + 3) + 8 * mcf.STATS_PER_INSTANCE
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    with mcf.Solver(S, n, B):
+        held = before - torch.cuda.mem_get_info()[0]
+    print(f"packed workspace S={S} n={n} B={B}: {held} bytes held, {each * B} used", flush=True)
+    assert held < 1.2 * each * B
+
+
 def zigzag(S, n):
     """Two unit chains a and d that the first two paths take; the third must
     enter at b, run back along a, over to c, back along d and out through e:

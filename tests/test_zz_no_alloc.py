@@ -5,8 +5,8 @@ Each case solves a batch with the ordinary handle entry point
 (gwtf_mcf_solve_batch) and with the no-allocation one on the same device
 inputs, twice in a row with the second batch smaller, and requires identical
 (F, cost, status) on every instance; the ordinary results are in turn checked
-against the CPU oracle.  The shapes cover the packed pass (with instances it
-hands to the fallback pass), the pipelined register pass and the grid pass.
+against the CPU oracle.  The shapes cover the packed pass (with instances its
+first launch passes on), the pipelined register pass and the grid pass.
 A batch whose workspace exceeds the array is refused with nothing enqueued.
 """
 import sys
@@ -75,7 +75,7 @@ def _check_pair(name, first, second, max_batch):
 
 def test_noalloc_packed_and_fallback():
     """8 x 8 batches on the packed pass, with instances whose link costs
-    exceed the packed bounds (solved by the fallback pass)."""
+    exceed its first launch's bounds (solved by the one after it)."""
     first = W.concat([W.config2(1800), W.random_small(200, 8, 8, seed=31, cost_hi=2600, supply_hi=40)])
     second = W.concat([W.config2(500, first=4000), W.random_small(40, 8, 8, seed=32, cost_hi=2600, supply_hi=40)])
     _check_pair("packed", first, second, max_batch=2000)
