@@ -144,6 +144,7 @@ struct gwtf_mcf {
     Workspace ws;
     int32_t *dense_arc = nullptr; // located batches: implied link delays, allocated on first use
     int32_t solved = 0; // batch size of the last successful solve (0 = none)
+    bool first_only = false; // see gwtf_internal_first_only
 };
 
 namespace {
@@ -336,7 +337,7 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
     } else {
         p.route_all = 1;
     }
-    if (need_fallback) {
+    if (need_fallback && !p.first_only) {
         p.list_slots = w.fallback_slots;
         size_t lds = scratch_bytes(fallback_waves(), n);
         if (lds > d.lds_max) return {GWTF_ERR_INVALID_ARG, "nodes_per_stage too large for LDS scratch", hipSuccess};
@@ -350,6 +351,7 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
 gwtf_status_t run_handle_passes(gwtf_mcf_t *h, SolveParams &p, const int32_t *loc, const int32_t *lat, int32_t L)
 {
     h->solved = 0;
+    p.first_only = h->first_only;
     const PassResult r = run_passes(h->ws, h->dev, h->shape.num_stages, h->shape.nodes_per_stage, h->stream, p,
                                     loc, lat, L);
     if (r.code == GWTF_ERR_DEVICE) return hip_fail(h, r.e, r.what);
@@ -616,6 +618,11 @@ extern "C" gwtf_status_t gwtf_mcf_get_passes(gwtf_mcf_t *h, int32_t first, int32
     return GWTF_OK;
 }
 
+extern "C" void gwtf_internal_first_only(gwtf_mcf_t *h, int32_t on)
+{
+    if (h) h->first_only = on != 0;
+}
+
 extern "C" void gwtf_mcf_destroy(gwtf_mcf_t *h)
 {
     if (!h) return;
@@ -785,6 +792,7 @@ extern "C" gwtf_status_t gwtf_mcf_resolve_churn(gwtf_mcf_t *h, const gwtf_mcf_ba
         p.tf_out = out->snk_flow;
     }
     p.work = work;
+    p.first_only = h->first_only;
     if ((e = launch_churn_resolve(p, h->stream)) != hipSuccess) return hip_fail(h, e, "churn re-solve launch");
     return GWTF_OK;
 }
@@ -847,6 +855,7 @@ extern "C" gwtf_status_t gwtf_mcf_simulate_heuristic(gwtf_mcf_t *h, const gwtf_m
         p.temperature = out->temperature;
         p.counters = out->counters;
     }
+    p.first_only = h->first_only;
     if ((e = launch_heuristic(p, h->stream)) != hipSuccess) return hip_fail(h, e, "heuristic simulation launch");
     return GWTF_OK;
 }

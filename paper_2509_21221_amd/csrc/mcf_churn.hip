@@ -522,7 +522,7 @@ hipError_t launch_churn_resolve(const ChurnParams &p, hipStream_t stream)
     q.passed_on = p.S <= kChurnPackedStages && p.n <= 16;
     if (q.passed_on) {
         const hipError_t e = launch_churn_packed(p, stream);
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess || p.first_only) return e;
     }
     hipLaunchKernelGGL(churn_kernel, dim3(p.B), dim3(threads), churn_lds_bytes(p.S, p.n), stream, q);
     return hipGetLastError();

@@ -996,7 +996,7 @@ hipError_t launch_heuristic(const HeurParams &p, hipStream_t stream)
             (void)hipGetLastError();
     hipLaunchKernelGGL(heuristic_kernel, dim3(unsigned(p.B)), dim3(64), fast, stream, p);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.max_slots <= kMaskSlots) return e; // no relay can hold more
+    if (e != hipSuccess || p.max_slots <= kMaskSlots || p.first_only) return e; // no relay can hold more
     hipLaunchKernelGGL(heuristic_general_kernel, dim3(unsigned(p.B)), dim3(64), general, stream, p);
     return hipGetLastError();
 }

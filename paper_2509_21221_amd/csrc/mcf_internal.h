@@ -37,6 +37,7 @@ struct SolveParams {
     int64_t list_slots;   // flow-list capacity of one instance
     int32_t route_all;    // LDS and fallback passes: solve every instance, ignoring route[]
     int32_t clock_khz;    // device wall-clock rate, for the phase timers
+    int32_t first_only;   // make only the first launch of a pass that has several (gwtf_internal_first_only)
 };
 
 // Per-instance counters written to SolveParams::stats: augmentations,
@@ -113,6 +114,11 @@ hipError_t launch_whatif_best(int32_t count, const int64_t *F, const int64_t *co
 // arc[b][k][i][j] = lat[b][loc[b][k][i]][loc[b][k+1][j]], -2 where invalid.
 hipError_t launch_located_expand(int32_t B, int32_t S, int32_t n, int32_t L, const int32_t *loc,
                                  const int32_t *lat, int32_t *arc, hipStream_t s);
+// For tests, exported but no part of the public ABI: while `on`, calls on the
+// handle make only the first launch of a pass that has several forms.  What
+// it passes on is then left with its mark: a route below 0 or above
+// kRouteSmall (packed and register pass), status -1 (churn re-solve, heuristic).
+extern "C" void gwtf_internal_first_only(struct gwtf_mcf *h, int32_t on);
 int fallback_waves();
 hipError_t set_lds_limits(size_t max_bytes);
 
@@ -132,6 +138,7 @@ struct HeurParams {
     int32_t *node_flow, *arc_flow, *used, *accepted;      // optional outputs
     double *temperature;                                  // optional [B][S][n]
     int64_t *counters;                                    // optional [B][4]
+    int32_t first_only;                                   // as in SolveParams
 };
 size_t heuristic_lds_bytes(int S, int n, int max_slots);
 hipError_t launch_heuristic(const HeurParams &p, hipStream_t stream);

@@ -547,7 +547,7 @@ template <int MAXS, int G, int ROWS> hipError_t launch_stages(const SolveParams 
     hipLaunchKernelGGL((solve_small_kernel<MAXS, G, ROWS>), dim3(unsigned((p.B + R - 1) / R)), dim3(64), lds, s, p, R,
                        S <= kPackedStages ? kRouteSmall : kRouteLds);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || p.first_only) return e;
     // The rest: what it holds per wave is bounded by 40 KB of LDS.
     int Rr = R;
     while (Rr > 1 && small_layout<MAXS, G, true>(S, n, Rr).total > 40 * 1024) Rr /= 2;

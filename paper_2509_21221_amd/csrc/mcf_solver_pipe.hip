@@ -1099,13 +1099,16 @@ hipError_t launch_pipe_pass(const SolveParams &p, hipStream_t s)
     // keyed variant first; the unscaled one takes the instances it passed on
     if (W == 8) {
         hipLaunchKernelGGL((solve_pipe_kernel<8, 1, true>), dim3(p.B), dim3(512), lds, s, p);
-        hipLaunchKernelGGL((solve_pipe_kernel<8, 1, false>), dim3(p.B), dim3(512), lds, s, p);
+        if (!p.first_only)
+            hipLaunchKernelGGL((solve_pipe_kernel<8, 1, false>), dim3(p.B), dim3(512), lds, s, p);
     } else if (P == 1) {
         hipLaunchKernelGGL((solve_pipe_kernel<16, 1, true>), dim3(p.B), dim3(1024), lds, s, p);
-        hipLaunchKernelGGL((solve_pipe_kernel<16, 1, false>), dim3(p.B), dim3(1024), lds, s, p);
+        if (!p.first_only)
+            hipLaunchKernelGGL((solve_pipe_kernel<16, 1, false>), dim3(p.B), dim3(1024), lds, s, p);
     } else {
         hipLaunchKernelGGL((solve_pipe_kernel<16, 2, true>), dim3(p.B), dim3(1024), lds, s, p);
-        hipLaunchKernelGGL((solve_pipe_kernel<16, 2, false>), dim3(p.B), dim3(1024), lds, s, p);
+        if (!p.first_only)
+            hipLaunchKernelGGL((solve_pipe_kernel<16, 2, false>), dim3(p.B), dim3(1024), lds, s, p);
     }
     return hipGetLastError();
 }
