@@ -276,6 +276,7 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
     p.state = w.state;
     p.state_stride = w.state_stride;
     p.clock_khz = d.clock_khz;
+    p.cus = d.cus;
 
     const int64_t worst = int64_t(std::max(S - 1, 0)) * n * n;
     bool need_fallback = true;
@@ -792,6 +793,7 @@ extern "C" gwtf_status_t gwtf_mcf_resolve_churn(gwtf_mcf_t *h, const gwtf_mcf_ba
         p.tf_out = out->snk_flow;
     }
     p.work = work;
+    p.cus = h->dev.cus;
     p.first_only = h->first_only;
     if ((e = launch_churn_resolve(p, h->stream)) != hipSuccess) return hip_fail(h, e, "churn re-solve launch");
     return GWTF_OK;

@@ -21,6 +21,7 @@ struct ChurnParams {
     int32_t *nf_out, *af_out, *sf_out, *tf_out;              // result flows, or all NULL
     int64_t *work;                                           // [B][4] or NULL
     int32_t passed_on;                                       // general form: only instances so marked
+    int32_t cus;                                             // compute units of the device
     int32_t first_only;                                      // as in SolveParams
 };
 size_t churn_lds_bytes(int S, int n);

@@ -647,7 +647,7 @@ template <int G> __global__ __launch_bounds__(64, 2) void churn_packed_kernel(Ch
 
 template <int G> hipError_t launch(const ChurnParams &p, hipStream_t stream)
 {
-    const int R = rows_per_wave(64 / G, p.B);
+    const int R = rows_per_wave(64 / G, p.B, p.cus);
     const size_t lds = small_layout<kChurnPackedStages, G, false>(p.S, p.n, R).total;
     hipLaunchKernelGGL((churn_packed_kernel<G>), dim3(unsigned((p.B + R - 1) / R)), dim3(64), lds, stream, p, R);
     return hipGetLastError();

@@ -37,6 +37,7 @@ struct SolveParams {
     int64_t list_slots;   // flow-list capacity of one instance
     int32_t route_all;    // LDS and fallback passes: solve every instance, ignoring route[]
     int32_t clock_khz;    // device wall-clock rate, for the phase timers
+    int32_t cus;          // compute units of the device
     int32_t first_only;   // make only the first launch of a pass that has several (gwtf_internal_first_only)
 };
 

@@ -201,16 +201,16 @@ __device__ __forceinline__ unsigned opaque_v(unsigned x)
     auto ridx = [=](int k, int ln, int d) GWTF_INLINE { return (k * R * G + ln) * G + d; };                            \
     (void)S, (void)nn, (void)gb, (void)j, (void)lidx, (void)ridx
 
-// Instances per wave of a batch: as few as keep it within kSmallSpreadWaves
-// waves (one per SIMD of the device), so that a small batch spreads over the
-// device, and all groups of the wave beyond that.  4,096 instances of 8 x 5
+// Instances per wave of a batch: as few as keep it within one wave per SIMD of
+// the device (four per CU), so that a small batch spreads over the device, and
+// all groups of the wave beyond that.  On 256 CUs: 4,096 instances of 8 x 5
 // (in the rest launch): 394 us within 512 waves, 375 within 1,024, 619 within
 // 2,048; 1,024 of 4 x 4: 60, 59 and 59 us.
-constexpr int kSmallSpreadWaves = 1024;
-inline int rows_per_wave(int groups, int B)
+inline int rows_per_wave(int groups, int B, int cus)
 {
+    const int waves = 4 * (cus > 0 ? cus : 256);
     int R = 1;
-    while (R < groups && (B + R - 1) / R > kSmallSpreadWaves) R *= 2;
+    while (R < groups && (B + R - 1) / R > waves) R *= 2;
     return R;
 }
 

@@ -541,7 +541,7 @@ __global__ __launch_bounds__(64, MAXS > 8 ? 1 : 2) void solve_small_rest_kernel(
 template <int MAXS, int G, int ROWS> hipError_t launch_stages(const SolveParams &p, size_t lds_max, hipStream_t s)
 {
     const int S = p.S, n = p.n;
-    const int R = rows_per_wave(64 / G, p.B);
+    const int R = rows_per_wave(64 / G, p.B, p.cus);
     const size_t lds = small_layout<MAXS, G, false>(S, n, R).total;
     if (lds > lds_max) return hipErrorInvalidValue;
     hipLaunchKernelGGL((solve_small_kernel<MAXS, G, ROWS>), dim3(unsigned((p.B + R - 1) / R)), dim3(64), lds, s, p, R,
