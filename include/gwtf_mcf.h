@@ -392,7 +392,6 @@ typedef struct {
 gwtf_status_t gwtf_mcf_simulate_heuristic(gwtf_mcf_t *h, const gwtf_mcf_batch_t *b,
                                           const gwtf_heur_config_t *cfg, const gwtf_heur_out_t *out);
 
-/* Frees the handle and its workspace after draining its stream; NULL-safe. */
 /* ---- Hand-off latency calibration ----
  *
  * Measures on `device` the least time one hop of the stage pipelines can
@@ -418,6 +417,7 @@ gwtf_status_t gwtf_mcf_simulate_heuristic(gwtf_mcf_t *h, const gwtf_mcf_batch_t 
 gwtf_status_t gwtf_mcf_calibrate_handoff(int32_t device, void *hip_stream, int32_t block_distance,
                                          double *latency_ns);
 
+/* Frees the handle and its workspace after draining its stream; NULL-safe. */
 void gwtf_mcf_destroy(gwtf_mcf_t *h);
 
 /* Text of the last error on this handle ("" if none); NULL handle gives the

@@ -29,8 +29,9 @@ def hipcc() -> str:
 # (2 % faster on the 64 x 512 instance); the register pass is not (the same
 # strategy spills three more registers there for no gain).  Its atomics are
 # issued by one lane already; combined over a wave, the arrival of an iteration
-# would be waited for before the next iteration's first reads go out (64 x 512
-# 855 -> 839 ms, four located 16 x 200 18.2 -> 17.8 ms).
+# would be waited for before the next iteration's first reads go out (in turn
+# with a build that combines them: a 64 x 512 1,261 / 1,227 ms, four located
+# 16 x 200 22.5 / 22.0 ms, quartiles within 0.2 % of these).
 EXTRA_FLAGS = {"mcf_solver_grid.hip": ["-mllvm", "-amdgpu-sched-strategy=max-memory-clause",
                                        "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
 

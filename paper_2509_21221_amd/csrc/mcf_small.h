@@ -11,9 +11,11 @@ constexpr int kPackedStages = 8;    // reported as the packed pass (and its rest
 constexpr int kSmallMaxStages = 16; // deeper pipelines up to here are reported as the LDS pass
 inline bool small_pass_fits(int S, int n) { return S >= 1 && S <= kSmallMaxStages && n <= 16; }
 // The launches of the pass, for n at most the number in the name: 4 and 8
-// lanes per instance, then 16 with a relaxation over that many rows.  With all
-// 16 rows 11,880 instances of 12 x 9 took 3.88 ms and 40,320 of 8 x 13 4.95 ms,
-// with 10 and 13 rows 3.63 and 4.87 ms.  They finish every instance of the batch.
+// lanes per instance, then 16 with a relaxation over that many rows.  In turn
+// with a build that always takes all 16: 4,096 instances of 12 x 9 1.24 against
+// 1.30 ms, 16,384 of 8 x 10 1.60 / 1.65 (10 rows); 16,384 of 8 x 13 2.29 / 2.33,
+// 4,096 of 12 x 13 2.10 / 2.16, 40,320 placements of 8 x 13 4.69 / 4.77 (13 rows),
+// quartiles within 0.3 % of these.  They finish every instance of the batch.
 hipError_t launch_small_pass4(const SolveParams &p, size_t lds_max, hipStream_t s);
 hipError_t launch_small_pass8(const SolveParams &p, size_t lds_max, hipStream_t s);
 hipError_t launch_small_pass10(const SolveParams &p, size_t lds_max, hipStream_t s);

@@ -30,9 +30,9 @@
 //    a new search, while their tree paths stay usable.  After up to kPathBatch
 //    paths the owners apply them to their nodes and lists.  With one path
 //    between barriers, and a second barrier for the flows that the owners
-//    wrote, 16 x 200 with 390 paths in 215 searches took 19.1 ms, now 17.5
+//    wrote, 16 x 200 with 390 paths in 215 searches took 19.1 ms, then 17.5
 //    (walks and augmentations 6.3 / 4.8 ms); 64 x 512 with 4,095 in 2,470
-//    spends 117 / 99 ms there and 857 / 857 ms altogether.
+//    spent 117 ms there, then 99 (not to be seen in its whole time).
 //
 // Memory ordering.  The L2 cache is private to each XCD, so every value one
 // workgroup writes for another (labels, predecessors, path, flows, control
@@ -913,7 +913,9 @@ template <bool kLocated> __global__ __launch_bounds__(kGridThreads, 1) void solv
 
                 // The reads that were still in flight when the wait above ended keep
                 // their registers up to here; reused earlier, they would hold the
-                // wave up until they are back (64 x 512: 907 ms, now 895).
+                // wave up until they are back (in turn with a build without this and
+                // without the scalar wave number: a 64 x 512 1,246 / 1,227 ms, a
+                // 24 x 384 31.6 / 31.1 ms).
                 asm volatile("" ::"v"(a0), "v"(a1), "v"(c0), "v"(c1), "v"(s0), "v"(s1));
 
                 // compute arcs of the owned nodes (group 0 of each column)
