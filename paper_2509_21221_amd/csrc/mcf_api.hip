@@ -265,7 +265,7 @@ struct PassResult {
 // selects the location-factored grid pass for shapes that use the grid),
 // with workspace `w` and the properties `d` of the current device.
 PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hipStream_t stream, SolveParams &p,
-                      const int32_t *loc, const int32_t *lat, int32_t L)
+                      const int32_t *loc, const int32_t *lat, int32_t L, bool first_only = false)
 {
     hipError_t e;
     p.route = w.route;
@@ -276,7 +276,7 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
     p.state = w.state;
     p.state_stride = w.state_stride;
     p.clock_khz = d.clock_khz;
-    p.cus = d.cus;
+    const LaunchInfo l{d.lds_max, d.cus, first_only};
 
     const int64_t worst = int64_t(std::max(S - 1, 0)) * n * n;
     bool need_fallback = true;
@@ -288,7 +288,7 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
         // outside the first one's bounds, so no fallback pass follows.
         p.list_slots = 0;
         p.route_all = 0;
-        if ((e = launch_small_pass(p, d.lds_max, stream)) != hipSuccess)
+        if ((e = launch_small_pass(p, l, stream)) != hipSuccess)
             return {GWTF_ERR_DEVICE, "packed solver launch", e};
         need_fallback = false;
     } else if (w.grid && grid_preferred(w, n, p.B)) {
@@ -325,7 +325,7 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
         // or more flow-list slots go to the fallback pass.
         p.list_slots = pipe_slots;
         p.route_all = 0;
-        if ((e = launch_pipe_pass(p, stream)) != hipSuccess) return {GWTF_ERR_DEVICE, "pipelined solver launch", e};
+        if ((e = launch_pipe_pass(p, l, stream)) != hipSuccess) return {GWTF_ERR_DEVICE, "pipelined solver launch", e};
         need_fallback = true;
     } else if (slots > 0) {
         p.list_slots = slots;
@@ -338,7 +338,7 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
     } else {
         p.route_all = 1;
     }
-    if (need_fallback && !p.first_only) {
+    if (need_fallback && !l.first_only) {
         p.list_slots = w.fallback_slots;
         size_t lds = scratch_bytes(fallback_waves(), n);
         if (lds > d.lds_max) return {GWTF_ERR_INVALID_ARG, "nodes_per_stage too large for LDS scratch", hipSuccess};
@@ -352,9 +352,8 @@ PassResult run_passes(const Workspace &w, const DeviceInfo &d, int S, int n, hip
 gwtf_status_t run_handle_passes(gwtf_mcf_t *h, SolveParams &p, const int32_t *loc, const int32_t *lat, int32_t L)
 {
     h->solved = 0;
-    p.first_only = h->first_only;
     const PassResult r = run_passes(h->ws, h->dev, h->shape.num_stages, h->shape.nodes_per_stage, h->stream, p,
-                                    loc, lat, L);
+                                    loc, lat, L, h->first_only);
     if (r.code == GWTF_ERR_DEVICE) return hip_fail(h, r.e, r.what);
     if (r.code != GWTF_OK) return fail(h, r.code, r.what);
     h->solved = p.B;
@@ -639,6 +638,8 @@ extern "C" const char *gwtf_mcf_last_error(const gwtf_mcf_t *h)
 
 namespace {
 
+LaunchInfo launch_info(const gwtf_mcf_t *h) { return {h->dev.lds_max, h->dev.cus, h->first_only}; }
+
 // S!/(S-m)! into *out; false when it does not fit in an int64.
 bool placement_count(int32_t S, int32_t m, int64_t *out)
 {
@@ -793,9 +794,7 @@ extern "C" gwtf_status_t gwtf_mcf_resolve_churn(gwtf_mcf_t *h, const gwtf_mcf_ba
         p.tf_out = out->snk_flow;
     }
     p.work = work;
-    p.cus = h->dev.cus;
-    p.first_only = h->first_only;
-    if ((e = launch_churn_resolve(p, h->stream)) != hipSuccess) return hip_fail(h, e, "churn re-solve launch");
+    if ((e = launch_churn_resolve(p, launch_info(h), h->stream)) != hipSuccess) return hip_fail(h, e, "churn re-solve launch");
     return GWTF_OK;
 }
 
@@ -857,7 +856,6 @@ extern "C" gwtf_status_t gwtf_mcf_simulate_heuristic(gwtf_mcf_t *h, const gwtf_m
         p.temperature = out->temperature;
         p.counters = out->counters;
     }
-    p.first_only = h->first_only;
-    if ((e = launch_heuristic(p, h->stream)) != hipSuccess) return hip_fail(h, e, "heuristic simulation launch");
+    if ((e = launch_heuristic(p, launch_info(h), h->stream)) != hipSuccess) return hip_fail(h, e, "heuristic simulation launch");
     return GWTF_OK;
 }

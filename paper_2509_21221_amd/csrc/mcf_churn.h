@@ -21,17 +21,15 @@ struct ChurnParams {
     int32_t *nf_out, *af_out, *sf_out, *tf_out;              // result flows, or all NULL
     int64_t *work;                                           // [B][4] or NULL
     int32_t passed_on;                                       // general form: only instances so marked
-    int32_t cus;                                             // compute units of the device
-    int32_t first_only;                                      // as in SolveParams
 };
 size_t churn_lds_bytes(int S, int n);
-hipError_t launch_churn_resolve(const ChurnParams &p, hipStream_t stream);
+hipError_t launch_churn_resolve(const ChurnParams &p, const LaunchInfo &l, hipStream_t stream);
 
 // The packed form: several instances per wave for S <= kChurnPackedStages,
 // n <= 16.  Marks what it does not hold with kChurnPassedOn in status_out; the
 // general form, launched after it, solves those.
 constexpr int kChurnPackedStages = 8;
 constexpr int32_t kChurnPassedOn = -1;
-hipError_t launch_churn_packed(const ChurnParams &p, hipStream_t stream);
+hipError_t launch_churn_packed(const ChurnParams &p, const LaunchInfo &l, hipStream_t stream);
 
 } // namespace gwtf

@@ -512,7 +512,7 @@ size_t churn_lds_bytes(int S, int n)
     return sizeof(int32_t) * (2 * size_t(S - 1) * n * (n + 1) + 3 * Sn + 4 * size_t(n) + 4 * V);
 }
 
-hipError_t launch_churn_resolve(const ChurnParams &p, hipStream_t stream)
+hipError_t launch_churn_resolve(const ChurnParams &p, const LaunchInfo &l, hipStream_t stream)
 {
     // A single wave for small instances: its barriers cost next to nothing
     // and more instances share a CU.
@@ -521,8 +521,8 @@ hipError_t launch_churn_resolve(const ChurnParams &p, hipStream_t stream)
     ChurnParams q = p;
     q.passed_on = p.S <= kChurnPackedStages && p.n <= 16;
     if (q.passed_on) {
-        const hipError_t e = launch_churn_packed(p, stream);
-        if (e != hipSuccess || p.first_only) return e;
+        const hipError_t e = launch_churn_packed(p, l, stream);
+        if (e != hipSuccess || l.first_only) return e;
     }
     hipLaunchKernelGGL(churn_kernel, dim3(p.B), dim3(threads), churn_lds_bytes(p.S, p.n), stream, q);
     return hipGetLastError();

@@ -645,9 +645,9 @@ template <int G> __global__ __launch_bounds__(64, 2) void churn_packed_kernel(Ch
     }
 }
 
-template <int G> hipError_t launch(const ChurnParams &p, hipStream_t stream)
+template <int G> hipError_t launch(const ChurnParams &p, const LaunchInfo &l, hipStream_t stream)
 {
-    const int R = rows_per_wave(64 / G, p.B, p.cus);
+    const int R = rows_per_wave(64 / G, p.B, l.cus);
     const size_t lds = small_layout<kChurnPackedStages, G, false>(p.S, p.n, R).total;
     hipLaunchKernelGGL((churn_packed_kernel<G>), dim3(unsigned((p.B + R - 1) / R)), dim3(64), lds, stream, p, R);
     return hipGetLastError();
@@ -655,10 +655,10 @@ template <int G> hipError_t launch(const ChurnParams &p, hipStream_t stream)
 
 } // namespace
 
-hipError_t launch_churn_packed(const ChurnParams &p, hipStream_t stream)
+hipError_t launch_churn_packed(const ChurnParams &p, const LaunchInfo &l, hipStream_t stream)
 {
-    if (p.n <= 4) return launch<4>(p, stream);
-    return p.n <= 8 ? launch<8>(p, stream) : launch<16>(p, stream);
+    if (p.n <= 4) return launch<4>(p, l, stream);
+    return p.n <= 8 ? launch<8>(p, l, stream) : launch<16>(p, l, stream);
 }
 
 } // namespace gwtf

@@ -987,7 +987,7 @@ size_t heuristic_lds_bytes(int S, int n, int max_slots)
     return general > masks ? general : masks;
 }
 
-hipError_t launch_heuristic(const HeurParams &p, hipStream_t stream)
+hipError_t launch_heuristic(const HeurParams &p, const LaunchInfo &l, hipStream_t stream)
 {
     const size_t fast = mask_layout(p.S, p.n, p.max_slots).total, general = heur_layout(p.S, p.n, p.max_slots).total;
     for (auto [f, bytes] : {std::pair{reinterpret_cast<const void *>(heuristic_kernel), fast},
@@ -999,7 +999,7 @@ hipError_t launch_heuristic(const HeurParams &p, hipStream_t stream)
     // The second launch costs 4 us where it finds nothing to do (one instance of
     // 8 x 5: one round 31 us before there were two forms, 36 now; 120 rounds 2,154
     // and 416).
-    if (e != hipSuccess || p.max_slots <= kMaskSlots || p.first_only) return e; // no relay can hold more
+    if (e != hipSuccess || p.max_slots <= kMaskSlots || l.first_only) return e; // no relay can hold more
     hipLaunchKernelGGL(heuristic_general_kernel, dim3(unsigned(p.B)), dim3(64), general, stream, p);
     return hipGetLastError();
 }

@@ -37,8 +37,14 @@ struct SolveParams {
     int64_t list_slots;   // flow-list capacity of one instance
     int32_t route_all;    // LDS and fallback passes: solve every instance, ignoring route[]
     int32_t clock_khz;    // device wall-clock rate, for the phase timers
-    int32_t cus;          // compute units of the device
-    int32_t first_only;   // make only the first launch of a pass that has several (gwtf_internal_first_only)
+};
+
+// What a pass's launches depend on besides (no part of the kernels' arguments:
+// two more words there cost the packed kernel 1.7 % on 16,384 of 8 x 8).
+struct LaunchInfo {
+    size_t lds_max = 0;
+    int cus = 0;             // compute units of the device
+    bool first_only = false; // make only the first launch (gwtf_internal_first_only)
 };
 
 // Per-instance counters written to SolveParams::stats: augmentations,
@@ -139,10 +145,9 @@ struct HeurParams {
     int32_t *node_flow, *arc_flow, *used, *accepted;      // optional outputs
     double *temperature;                                  // optional [B][S][n]
     int64_t *counters;                                    // optional [B][4]
-    int32_t first_only;                                   // as in SolveParams
 };
 size_t heuristic_lds_bytes(int S, int n, int max_slots);
-hipError_t launch_heuristic(const HeurParams &p, hipStream_t stream);
+hipError_t launch_heuristic(const HeurParams &p, const LaunchInfo &l, hipStream_t stream);
 
 // Hand-off latency calibration (mcf_calibrate.hip): one-way latencies in
 // ns of an LDS hand-off between two waves, and of device-scope hand-offs

@@ -39,6 +39,6 @@ __host__ __device__ inline PipeLayout pipe_layout(int S, int waves, int64_t slot
 
 bool pipe_pass_fits(int S, int n);
 int64_t pipe_pass_slots(int S, size_t lds_max); // flow-list slots that fit beside the rest
-hipError_t launch_pipe_pass(const SolveParams &p, hipStream_t s);
+hipError_t launch_pipe_pass(const SolveParams &p, const LaunchInfo &l, hipStream_t s);
 
 } // namespace gwtf

@@ -16,17 +16,17 @@ inline bool small_pass_fits(int S, int n) { return S >= 1 && S <= kSmallMaxStage
 // 1.30 ms, 16,384 of 8 x 10 1.60 / 1.65 (10 rows); 16,384 of 8 x 13 2.29 / 2.33,
 // 4,096 of 12 x 13 2.10 / 2.16, 40,320 placements of 8 x 13 4.69 / 4.77 (13 rows),
 // quartiles within 0.3 % of these.  They finish every instance of the batch.
-hipError_t launch_small_pass4(const SolveParams &p, size_t lds_max, hipStream_t s);
-hipError_t launch_small_pass8(const SolveParams &p, size_t lds_max, hipStream_t s);
-hipError_t launch_small_pass10(const SolveParams &p, size_t lds_max, hipStream_t s);
-hipError_t launch_small_pass13(const SolveParams &p, size_t lds_max, hipStream_t s);
-hipError_t launch_small_pass16(const SolveParams &p, size_t lds_max, hipStream_t s);
-inline hipError_t launch_small_pass(const SolveParams &p, size_t lds_max, hipStream_t s)
+hipError_t launch_small_pass4(const SolveParams &p, const LaunchInfo &l, hipStream_t s);
+hipError_t launch_small_pass8(const SolveParams &p, const LaunchInfo &l, hipStream_t s);
+hipError_t launch_small_pass10(const SolveParams &p, const LaunchInfo &l, hipStream_t s);
+hipError_t launch_small_pass13(const SolveParams &p, const LaunchInfo &l, hipStream_t s);
+hipError_t launch_small_pass16(const SolveParams &p, const LaunchInfo &l, hipStream_t s);
+inline hipError_t launch_small_pass(const SolveParams &p, const LaunchInfo &l, hipStream_t s)
 {
-    if (p.n <= 4) return launch_small_pass4(p, lds_max, s);
-    if (p.n <= 8) return launch_small_pass8(p, lds_max, s);
-    if (p.n <= 10) return launch_small_pass10(p, lds_max, s);
-    return p.n <= 13 ? launch_small_pass13(p, lds_max, s) : launch_small_pass16(p, lds_max, s);
+    if (p.n <= 4) return launch_small_pass4(p, l, s);
+    if (p.n <= 8) return launch_small_pass8(p, l, s);
+    if (p.n <= 10) return launch_small_pass10(p, l, s);
+    return p.n <= 13 ? launch_small_pass13(p, l, s) : launch_small_pass16(p, l, s);
 }
 
 } // namespace gwtf

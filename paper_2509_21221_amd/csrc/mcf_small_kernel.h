@@ -538,16 +538,16 @@ __global__ __launch_bounds__(64, MAXS > 8 ? 1 : 2) void solve_small_rest_kernel(
     }
 }
 
-template <int MAXS, int G, int ROWS> hipError_t launch_stages(const SolveParams &p, size_t lds_max, hipStream_t s)
+template <int MAXS, int G, int ROWS> hipError_t launch_stages(const SolveParams &p, const LaunchInfo &l, hipStream_t s)
 {
     const int S = p.S, n = p.n;
-    const int R = rows_per_wave(64 / G, p.B, p.cus);
+    const int R = rows_per_wave(64 / G, p.B, l.cus);
     const size_t lds = small_layout<MAXS, G, false>(S, n, R).total;
-    if (lds > lds_max) return hipErrorInvalidValue;
+    if (lds > l.lds_max) return hipErrorInvalidValue;
     hipLaunchKernelGGL((solve_small_kernel<MAXS, G, ROWS>), dim3(unsigned((p.B + R - 1) / R)), dim3(64), lds, s, p, R,
                        S <= kPackedStages ? kRouteSmall : kRouteLds);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.first_only) return e;
+    if (e != hipSuccess || l.first_only) return e;
     // The rest: what it holds per wave is bounded by 40 KB of LDS.
     int Rr = R;
     while (Rr > 1 && small_layout<MAXS, G, true>(S, n, Rr).total > 40 * 1024) Rr /= 2;
@@ -567,17 +567,17 @@ template <int MAXS, int G, int ROWS> hipError_t launch_stages(const SolveParams 
     // 16,384 of them 41 against 242 ms).
     const bool general = S <= kPackedStages || R == 1;
     const size_t rows = small_layout<MAXS, G, true>(S, n, Rr).total, rest = general ? std::max(rows, body) : rows;
-    if (rows > lds_max || body > lds_max) return hipErrorInvalidValue;
+    if (rows > l.lds_max || body > l.lds_max) return hipErrorInvalidValue;
     hipLaunchKernelGGL((solve_small_rest_kernel<MAXS, G, ROWS>), dim3(unsigned((p.B + Rr - 1) / Rr)), dim3(64), rest, s, q,
                        Rr, S <= kPackedStages ? kRouteGlobal : kRouteLds, general);
     if ((e = hipGetLastError()) != hipSuccess || general) return e;
     return launch_lds_pass(q, 1, body, s);
 }
 
-template <int G, int ROWS> hipError_t launch_group(const SolveParams &p, size_t lds_max, hipStream_t s)
+template <int G, int ROWS> hipError_t launch_group(const SolveParams &p, const LaunchInfo &l, hipStream_t s)
 {
-    return p.S <= kPackedStages ? launch_stages<kPackedStages, G, ROWS>(p, lds_max, s)
-                                : launch_stages<kSmallMaxStages, G, ROWS>(p, lds_max, s);
+    return p.S <= kPackedStages ? launch_stages<kPackedStages, G, ROWS>(p, l, s)
+                                : launch_stages<kSmallMaxStages, G, ROWS>(p, l, s);
 }
 
 } // namespace

@@ -1091,7 +1091,7 @@ int64_t pipe_pass_slots(int S, size_t lds_max)
     return std::min<int64_t>(int64_t((lds_max - fixed) / 8), 65535);
 }
 
-hipError_t launch_pipe_pass(const SolveParams &p, hipStream_t s)
+hipError_t launch_pipe_pass(const SolveParams &p, const LaunchInfo &l, hipStream_t s)
 {
     int W, P;
     pipe_shape(p.S, W, P);
@@ -1099,15 +1099,15 @@ hipError_t launch_pipe_pass(const SolveParams &p, hipStream_t s)
     // keyed variant first; the unscaled one takes the instances it passed on
     if (W == 8) {
         hipLaunchKernelGGL((solve_pipe_kernel<8, 1, true>), dim3(p.B), dim3(512), lds, s, p);
-        if (!p.first_only)
+        if (!l.first_only)
             hipLaunchKernelGGL((solve_pipe_kernel<8, 1, false>), dim3(p.B), dim3(512), lds, s, p);
     } else if (P == 1) {
         hipLaunchKernelGGL((solve_pipe_kernel<16, 1, true>), dim3(p.B), dim3(1024), lds, s, p);
-        if (!p.first_only)
+        if (!l.first_only)
             hipLaunchKernelGGL((solve_pipe_kernel<16, 1, false>), dim3(p.B), dim3(1024), lds, s, p);
     } else {
         hipLaunchKernelGGL((solve_pipe_kernel<16, 2, true>), dim3(p.B), dim3(1024), lds, s, p);
-        if (!p.first_only)
+        if (!l.first_only)
             hipLaunchKernelGGL((solve_pipe_kernel<16, 2, false>), dim3(p.B), dim3(1024), lds, s, p);
     }
     return hipGetLastError();

@@ -4,9 +4,9 @@
 
 namespace gwtf {
 
-hipError_t launch_small_pass8(const SolveParams &p, size_t lds_max, hipStream_t s)
+hipError_t launch_small_pass8(const SolveParams &p, const LaunchInfo &l, hipStream_t s)
 {
-    return launch_group<8, 8>(p, lds_max, s);
+    return launch_group<8, 8>(p, l, s);
 }
 
 } // namespace gwtf
